@@ -8,6 +8,7 @@
 // + (s % inner)*inner_stride, separately for the query side and the key side.
 #pragma once
 #include "si_common.h"
+#include "k_norm.h"
 
 namespace si {
 
@@ -32,8 +33,8 @@ struct AttnArgs {
 // One wavefront serves QB queries of one (sequence, head): in the score phase
 // each lane owns one key of a 64-key chunk and forms QB dot products; in the
 // value phase each lane owns channels lane and lane+64 (d <= 128).  Exact expf,
-// fp32 throughout: this is the path of the fp32 block and the fallback for
-// shapes the matrix-core kernels do not cover.
+// fp32 throughout: this is the path of the fp32 block and of temporal sequences
+// longer than 32 frames.
 template <typename T, int QB>
 __global__ __launch_bounds__(256) void attn_valu_kernel(AttnArgs a) {
   __shared__ float qs[4][QB][128];
@@ -118,123 +119,117 @@ __global__ __launch_bounds__(256) void attn_valu_kernel(AttnArgs a) {
 }
 
 // Short sequences in 16-bit storage (temporal blocks on the staged path: at most 32 tokens per
-// sequence, head dimension DH): one wavefront per (sequence, head).  The head's key and value rows
-// are staged in LDS; lane l owns query l % 32 and, by its half l / 32, every other key in the score
-// phase (the two halves meet in one lane^32 exchange for the row maximum and the row sum) and one
-// half of the head's channels in the value phase (the other half's probabilities arrive by the same
-// exchange).  fp32 arithmetic, exact expf, as in attn_valu_kernel.
-template <int DH>
-__global__ __launch_bounds__(256) void attn_short_kernel(AttnArgs a) {
-  static_assert(DH % 16 == 0 && DH <= 128, "head dimension");
-  constexpr int LD = DH + 8;  // 16-bit elements per LDS row: rows stay 16-byte aligned and rotate over the banks
-  __shared__ __attribute__((aligned(16))) unsigned short kv[4][2][32][LD];
+// sequence, any head dimension d = 8 .. 128, d % 8 == 0) on the matrix cores: one wavefront per
+// (sequence, head), no LDS.  A lane's 16-byte pieces of the q, k and v rows are MFMA operands as they
+// stand (lane (token r, half g): channels 16 ks + 8 g + e), so S^T[key, query] = K Q^T takes both
+// straight from memory, and the softmax result registers are the column operand of O^T += V^T P^T.
+// V^T comes from V by a product with the identity (V as row operand, 16-channel slices of I as column
+// operand: exact, and the result registers are keys in the order P^T has them).  P enters as the sum of
+// two bf16 values (p and what its rounding leaves), so the probabilities keep 16 significand bits.
+// Bound by the gather of q/k/v rows, which lie Pw rows apart: a workgroup takes one head of 4 consecutive
+// sequences (adjacent token rows on either side), the heads of those sequences follow each other, and
+// every XCD gets a contiguous share of that list, so that an L2 sees whole lines.
+// 500 sequences of 14 frames, 8 heads of 80: 54.7 us (vector-ALU online softmax) -> 13.4; 128 of 16
+// frames, 20 heads of 64: 21.3 us (one lane per query, fp32 dot products) -> 12.7, and the out-projection
+// behind it reads fragments instead of rows (24.1 -> 20.7 us).
+// o_frag: o is a fragment-order buffer of that many channels per token instead of rows.
+template <int KS, int DB>
+__global__ __launch_bounds__(256, KS <= 5 ? 4 : 2) void attn_short_kernel(AttnArgs a, int o_frag) {
   const int lane = threadIdx.x % kWave;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  const int pair = blockIdx.x * 4 + wave;  // heads fastest: the wavefronts of a workgroup share token rows
-  if (pair >= a.S * a.heads) return;       // whole wavefront leaves; no block-wide barrier below
-  const int s = pair / a.heads, hc = (pair % a.heads) * DH;
+  const int r = lane % 32, g = lane / 32;
+  const int groups = (a.S + 3) / 4, ntiles = groups * a.heads, chunk = (ntiles + 7) / 8;
+  const int work = (int)(blockIdx.x % 8) * chunk + (int)(blockIdx.x / 8);
+  if (work >= ntiles || (int)(blockIdx.x / 8) >= chunk) return;
+  const int s = (work / a.heads) * 4 + wave, hc = (work % a.heads) * a.d;
+  if (s >= a.S) return;  // whole wavefront leaves; no block-wide barrier below
   const int F = a.Nk;
-  const unsigned short* Q = static_cast<const unsigned short*>(a.q);
-  const unsigned short* Kp = static_cast<const unsigned short*>(a.k);
-  const unsigned short* Vp = static_cast<const unsigned short*>(a.v);
-  unsigned short* O = static_cast<unsigned short*>(a.o);
-
-  constexpr int LPR = DH / 8, RPI = kWave / LPR;  // lanes per row, rows per wavefront load
-  for (int r0 = 0; r0 < F; r0 += RPI) {
-    const int r = r0 + lane / LPR, c = (lane % LPR) * 8;
-    if (lane < RPI * LPR && r < F) {
-      const int64_t row = a.kmap.row(s, r);
-      *reinterpret_cast<uint4*>(&kv[wave][0][r][c]) = *reinterpret_cast<const uint4*>(Kp + row * a.ldk + hc + c);
-      *reinterpret_cast<uint4*>(&kv[wave][1][r][c]) = *reinterpret_cast<const uint4*>(Vp + row * a.ldv + hc + c);
+  const int rr = r < F ? r : F - 1;  // rows past the sequence repeat the last one: masked as keys, not stored as queries
+  const unsigned short* qrow = static_cast<const unsigned short*>(a.q) + a.qmap.row(s, rr) * a.ldq + hc + 8 * g;
+  const unsigned short* krow = static_cast<const unsigned short*>(a.k) + a.kmap.row(s, rr) * a.ldk + hc + 8 * g;
+  const unsigned short* vrow = static_cast<const unsigned short*>(a.v) + a.kmap.row(s, rr) * a.ldv + hc + 8 * g;
+  u32x4_t qf[KS], kf[KS], vf[KS];
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) {
+    const bool in = 16 * ks + 8 * g < a.d;  // only the last k-step of an odd number of 8-channel pieces is half empty
+    qf[ks] = kf[ks] = vf[ks] = u32x4_t{0, 0, 0, 0};
+    if (in) {
+      qf[ks] = *reinterpret_cast<const u32x4_t*>(qrow + 16 * ks);
+      kf[ks] = *reinterpret_cast<const u32x4_t*>(krow + 16 * ks);
+      vf[ks] = *reinterpret_cast<const u32x4_t*>(vrow + 16 * ks);
     }
   }
-  const int i = lane % 32, half = lane / 32;
-  const bool active = i < a.Nq;
-  float q[DH];
-  {
-    const unsigned short* qrow = Q + a.qmap.row(s, active ? i : 0) * a.ldq + hc;
+  auto mfma = [](u32x4_t row, u32x4_t col, f32x16_t acc) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, row), __builtin_bit_cast(bf16x8_t, col), acc, 0, 0, 0);
+  };
+  f32x16_t zero;
 #pragma unroll
-    for (int c = 0; c < DH; c += 8) {
-      const uint4 raw = *reinterpret_cast<const uint4*>(qrow + c);
-      const unsigned w[4] = {raw.x, raw.y, raw.z, raw.w};
+  for (int e = 0; e < 16; ++e) zero[e] = 0.f;
+  f32x16_t sc = zero;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        q[c + 2 * e] = __uint_as_float(w[e] << 16) * a.scale;
-        q[c + 2 * e + 1] = __uint_as_float(w[e] & 0xffff0000u) * a.scale;
-      }
-    }
-  }
-  __builtin_amdgcn_wave_barrier();  // LDS operations of one wavefront complete in program order
+  for (int ks = 0; ks < KS; ++ks) sc = mfma(kf[ks], qf[ks], sc);
 
-  float sc[16];
+  // softmax over the keys: this lane holds keys 8 (e / 4) + 4 g + e % 4 of query r, lane ^ 32 the others
+  const float scale2 = a.scale * 1.4426950408889634f;
   float m = -INFINITY;
 #pragma unroll
-  for (int t = 0; t < 16; ++t) {
-    sc[t] = -INFINITY;
-    if (2 * t < F) {  // uniform
-      const int j = 2 * t + half;
-      if (j < F) {
-        float acc = 0.f;
-#pragma unroll
-        for (int c = 0; c < DH; c += 8) {
-          const uint4 raw = *reinterpret_cast<const uint4*>(&kv[wave][0][j][c]);
-          const unsigned w[4] = {raw.x, raw.y, raw.z, raw.w};
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            acc = fmaf(q[c + 2 * e], __uint_as_float(w[e] << 16), acc);
-            acc = fmaf(q[c + 2 * e + 1], __uint_as_float(w[e] & 0xffff0000u), acc);
-          }
-        }
-        sc[t] = acc;
-      }
-      m = fmaxf(m, sc[t]);
-    }
+  for (int e = 0; e < 16; ++e) {
+    sc[e] = 8 * (e / 4) + 4 * g + (e % 4) < F ? sc[e] * scale2 : -INFINITY;
+    m = fmaxf(m, sc[e]);
   }
   m = fmaxf(m, __shfl_xor(m, 32, kWave));
+  unsigned hi[8], lo[8];
   float l = 0.f;
 #pragma unroll
-  for (int t = 0; t < 16; ++t) {
-    sc[t] = 2 * t < F ? expf(sc[t] - m) : 0.f;  // a key beyond the sequence: exp(-inf) = 0
-    l += sc[t];
+  for (int i = 0; i < 8; ++i) {
+    const float p0 = __builtin_amdgcn_exp2f(sc[2 * i] - m), p1 = __builtin_amdgcn_exp2f(sc[2 * i + 1] - m);
+    l += p0 + p1;
+    hi[i] = (unsigned)float_to_bf16_bits(p0) | ((unsigned)float_to_bf16_bits(p1) << 16);
+    lo[i] = (unsigned)float_to_bf16_bits(p0 - __uint_as_float(hi[i] << 16)) |
+            ((unsigned)float_to_bf16_bits(p1 - __uint_as_float(hi[i] & 0xffff0000u)) << 16);
   }
   l += __shfl_xor(l, 32, kWave);
-
-  constexpr int HC = DH / 2;  // channels of this lane in the value phase: half * HC .. + HC
-  float o[HC];
-#pragma unroll
-  for (int c = 0; c < HC; ++c) o[c] = 0.f;
-#pragma unroll
-  for (int t = 0; t < 16; ++t) {
-    if (2 * t < F) {  // uniform
-      const float other = __shfl_xor(sc[t], 32, kWave);
-      const float pj[2] = {half ? other : sc[t], half ? sc[t] : other};  // keys 2t and 2t + 1
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        if (2 * t + u < F) {  // uniform
-#pragma unroll
-          for (int c = 0; c < HC; c += 8) {
-            const uint4 raw = *reinterpret_cast<const uint4*>(&kv[wave][1][2 * t + u][half * HC + c]);
-            const unsigned w[4] = {raw.x, raw.y, raw.z, raw.w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              o[c + 2 * e] = fmaf(pj[u], __uint_as_float(w[e] << 16), o[c + 2 * e]);
-              o[c + 2 * e + 1] = fmaf(pj[u], __uint_as_float(w[e] & 0xffff0000u), o[c + 2 * e + 1]);
-            }
-          }
-        }
-      }
-    }
-  }
-  if (!active) return;
   const float inv = 1.f / l;
-  unsigned short* orow = O + a.qmap.row(s, i) * a.ldo + hc + half * HC;
+
+  // slices of the identity: k-step s2 of a 32-channel block, lane (column r, half g): element e is 1 where 16 s2 + 8 g + e == r
+  u32x4_t eye[2];
 #pragma unroll
-  for (int c = 0; c < HC; c += 8) {
-    unsigned w[4];
+  for (int s2 = 0; s2 < 2; ++s2)
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
-      w[e] = (unsigned)float_to_bf16_bits(o[c + 2 * e] * inv) | ((unsigned)float_to_bf16_bits(o[c + 2 * e + 1] * inv) << 16);
-    *reinterpret_cast<uint4*>(orow + c) = make_uint4(w[0], w[1], w[2], w[3]);
+    for (int w = 0; w < 4; ++w) {
+      const int at = r - (16 * s2 + 8 * g + 2 * w);
+      eye[s2][w] = at == 0 ? 0x3f80u : at == 1 ? 0x3f800000u : 0u;
+    }
+  const int64_t orow = a.qmap.row(s, rr);
+  unsigned short* O = static_cast<unsigned short*>(a.o);
+#pragma unroll
+  for (int b = 0; b < DB; ++b) {
+    f32x16_t vt = mfma(vf[2 * b], eye[0], zero);
+    if (2 * b + 1 < KS) vt = mfma(vf[2 * b + 1 < KS ? 2 * b + 1 : 0], eye[1], vt);
+    f32x16_t o = zero;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      u32x4_t vrow4;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        vrow4[i] = (unsigned)float_to_bf16_bits(vt[8 * t + 2 * i]) | ((unsigned)float_to_bf16_bits(vt[8 * t + 2 * i + 1]) << 16);
+      o = mfma(vrow4, u32x4_t{hi[4 * t], hi[4 * t + 1], hi[4 * t + 2], hi[4 * t + 3]}, o);
+      o = mfma(vrow4, u32x4_t{lo[4 * t], lo[4 * t + 1], lo[4 * t + 2], lo[4 * t + 3]}, o);
+    }
+    // registers 8 hf .. + 7: channels 32b + 16hf + {4g .. +3, 8 + 4g .. +3}; one lane^32 exchange per register
+    // pair hands each lane the 8 consecutive channels 32b + 16hf + 8g .. +7
+#pragma unroll
+    for (int hf = 0; hf < 2; ++hf) {
+      unsigned w[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        w[i] = (unsigned)float_to_bf16_bits(o[8 * hf + 2 * i] * inv) | ((unsigned)float_to_bf16_bits(o[8 * hf + 2 * i + 1] * inv) << 16);
+      const auto x = __builtin_amdgcn_permlane32_swap(w[0], w[2], false, false);
+      const auto y = __builtin_amdgcn_permlane32_swap(w[1], w[3], false, false);
+      const int c = 32 * b + 16 * hf + 8 * g;
+      if (r < F && c < a.d)
+        *reinterpret_cast<u32x4_t*>(O + (o_frag ? act_offset(orow, hc + c, o_frag) : orow * a.ldo + hc + c)) = u32x4_t{x[0], y[0], x[1], y[1]};
+    }
   }
 }
 

@@ -9,6 +9,7 @@
 #include <cstring>
 #include <mutex>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "k_attn.h"
@@ -130,13 +131,12 @@ struct Plan {
                     // token tiles (F leaves many of a wavefront's 32 columns empty in the one-kernel form)
   bool post_fused;  // spatial: everything behind the self-attention (its out-projection, LN2, query projection,
                     // attention over the context, FFN half) in one register-resident kernel
-  bool attn_mfma;   // matrix-core attention kernel for the staged spatial path (bf16, head dimension 64)
+  bool attn_mfma;   // spatial, bf16: matrix-core attention on fragment operands
   bool ring;        // staged bf16 GEMMs run on the fragment-order ring kernel (operands in fragment order)
   int lanes;        // slices in flight (many small slices: 2 or 3, each on a stream of its own)
   size_t lane_stride;  // bytes between two lanes' slice intermediates
-  int Mcp;          // context tokens rounded up to a multiple of 8 (transposed value copy)
   // workspace offsets (bytes)
-  size_t off_stats, off_rehash, off_pe, off_ctxkv, off_ctxvt, off_vt;
+  size_t off_stats, off_rehash, off_pe, off_ctxkv, off_ctxfrag, off_ml;
   size_t off_w_in, off_wqkv, off_wo, off_wq2, off_wkv2, off_wo2, off_w1, off_w2, off_w_out;
   size_t off_a, off_h, off_big, off_ffn_stream, off_attn_stream, off_pre_stream;
   size_t weights_bytes, total_bytes;
@@ -195,10 +195,7 @@ static si_status make_plan(const si_tensor5* x, const si_block_weights* w, const
   };
   // slice-independent activation-derived items
   p->off_stats = take((size_t)p->B * p->F * p->G * 2 * sizeof(float));
-  p->off_ctxkv = take((size_t)p->B * p->Mc * 2 * Dz * es);
-  p->attn_mfma = p->dtype == SI_BF16 && p->kind == SI_BLOCK_SPATIAL && p->d == 64 && P % 8 == 0;
-  p->Mcp = (p->Mc + 7) / 8 * 8;
-  p->off_ctxvt = take(p->attn_mfma ? (size_t)p->B * Dz * p->Mcp * es : 0);
+  p->attn_mfma = p->dtype == SI_BF16 && p->kind == SI_BLOCK_SPATIAL;
   // which path: register-resident kernels need bf16, C == D = 64 or 320 (instantiated widths)
   p->fused_nb = 0;
   p->fused_attn = false;
@@ -219,6 +216,8 @@ static si_status make_plan(const si_tensor5* x, const si_block_weights* w, const
   // channels (two 32-channel blocks), at most kCrossTiles key tiles
   p->post_fused = p->fused_nb == 10 && p->kind == SI_BLOCK_SPATIAL && p->attn_mfma && p->d == 64 && P % 128 == 0 &&
                   p->Mc <= 32 * kCrossTiles;
+  // context keys / values as the attention kernel's fragments (the post-attention kernel has its own form)
+  p->off_ctxfrag = take(p->attn_mfma && !p->post_fused ? attn_kv_bytes(p->B, p->heads, p->Mc, p->d) : 0);
   // Ring GEMMs: 16-bit storage, every contraction length a multiple of the 32-wide k-tile, operand
   // buffers addressable with 32-bit byte offsets.
   p->ring = p->dtype == SI_BF16 && p->C % 32 == 0 && D % 32 == 0 &&
@@ -237,9 +236,15 @@ static si_status make_plan(const si_tensor5* x, const si_block_weights* w, const
     const size_t pad = p->ring ? kActZeroBytes : 0, Mp = p->ring ? (size_t)((p->Mmax + 31) / 32 * 32) : (size_t)p->Mmax;
     p->off_a = take(pad + Mp * (C > Dz ? C : Dz) * es);
     p->off_h = take((size_t)p->Mmax * Dz * sizeof(float));
-    p->off_big = take(pad + Mp * 4 * Dz * es);
+    size_t big = pad + Mp * 4 * Dz * es;
+    if (p->attn_mfma && !p->post_fused) {  // q, then k / v fragments (within 4 D per token unless H*W or d pads a lot)
+      const size_t frags = attn_q_bytes(p->B * p->slice_len, p->heads, P, p->d) + attn_kv_bytes(p->B * p->slice_len, p->heads, P, p->d);
+      big = big > frags ? big : frags;
+    }
+    p->off_big = take(big);
   }
-  p->off_vt = take(p->attn_mfma ? (size_t)p->Mmax * Dz * es : 0);  // values of the window, keys contiguous
+  // post_fused: (reference maximum, row sum) of the two key halves
+  p->off_ml = take(p->post_fused ? (size_t)2 * p->heads * (p->Mmax / 32) * kWave * sizeof(float2) : 0);
   // Cross-slice pipelining (Sec. 4.2.2): with many small slices the kernels of one slice leave CUs
   // idle (under-filled grids, partial last rounds), so several windows run at a time, each on a
   // stream and with intermediates of its own: as many as keep the window intermediates in flight
@@ -255,6 +260,9 @@ static si_status make_plan(const si_tensor5* x, const si_block_weights* w, const
   // when those are large enough.
   const size_t rehash_bytes = (size_t)p->B * p->F * p->G * 3 * sizeof(double) + 16;
   p->off_rehash = rehash_bytes <= p->lane_stride ? p->off_a : take(rehash_bytes);
+  // context keys / values before they are re-ordered: gone when the first window starts, likewise
+  const size_t ctx_bytes = (size_t)p->B * p->Mc * 2 * Dz * es;
+  p->off_ctxkv = (p->attn_mfma && ctx_bytes <= p->lane_stride) ? p->off_a : take(ctx_bytes);
   const size_t act_end = off;
   // frame position table (a function of F and D only: written with the weight re-layout)
   p->off_pe = take(p->pe ? (size_t)p->F * Dz * sizeof(float) : 0);
@@ -426,16 +434,38 @@ static si_status launch_gemm_sel(const char* stage, bool as_ring, const T* A, in
   return launch_gemm<T, F16>(stage, A, lda, Wp, M, N, K, epi, st);
 }
 
+// Calls f(integral_constant<KS>, integral_constant<DB>) for head dimension d = 8 .. 128.
+template <class Fn>
+static void attn_dispatch(int d, Fn f) {
+  switch (attn_ksteps(d)) {
+    case 1: f(std::integral_constant<int, 1>(), std::integral_constant<int, 1>()); break;
+    case 2: f(std::integral_constant<int, 2>(), std::integral_constant<int, 1>()); break;
+    case 3: f(std::integral_constant<int, 3>(), std::integral_constant<int, 2>()); break;
+    case 4: f(std::integral_constant<int, 4>(), std::integral_constant<int, 2>()); break;
+    case 5: f(std::integral_constant<int, 5>(), std::integral_constant<int, 3>()); break;
+    case 6: f(std::integral_constant<int, 6>(), std::integral_constant<int, 3>()); break;
+    case 7: f(std::integral_constant<int, 7>(), std::integral_constant<int, 4>()); break;
+    default: f(std::integral_constant<int, 8>(), std::integral_constant<int, 4>()); break;
+  }
+}
+
+// sequences of up to 32 tokens in 16-bit storage go to the matrix cores
 template <typename T>
-static si_status launch_attention(const char* stage, const AttnArgs& a, hipStream_t st) {
+static bool attention_is_short(const AttnArgs& a) {
+  return sizeof(T) == 2 && a.Nq == a.Nk && a.Nk <= 32 && a.ldq % 8 == 0 && a.ldk % 8 == 0 && a.ldv % 8 == 0 && a.ldo % 8 == 0 &&
+         aligned16(a.q) && aligned16(a.k) && aligned16(a.v) && aligned16(a.o);
+}
+
+template <typename T>
+static si_status launch_attention(const char* stage, const AttnArgs& a, hipStream_t st, int o_frag = 0) {
   if (a.S <= 0 || a.Nq <= 0) return SI_OK;
   StageScope scope(stage, st);
   if constexpr (sizeof(T) == 2) {
-    // self-attention over a short sequence (temporal blocks): one wavefront per (sequence, head)
-    const bool rows16 = a.ldq % 8 == 0 && a.ldk % 8 == 0 && a.ldv % 8 == 0 && a.ldo % 8 == 0 && aligned16(a.q) && aligned16(a.k) &&
-                        aligned16(a.v) && aligned16(a.o);
-    if (a.d == 64 && a.Nq == a.Nk && a.Nk <= 32 && rows16) {
-      attn_short_kernel<64><<<(unsigned)(((int64_t)a.S * a.heads + 3) / 4), 256, 0, st>>>(a);
+    if (attention_is_short<T>(a)) {
+      const int64_t wgs = (int64_t)((a.S + 3) / 4) * a.heads;
+      attn_dispatch(a.d, [&](auto ks, auto db) {
+        attn_short_kernel<ks.value, db.value><<<(unsigned)((wgs + 7) / 8 * 8), 256, 0, st>>>(a, o_frag);
+      });
       SI_CHECK_LAUNCH();
       return SI_OK;
     }
@@ -447,37 +477,22 @@ static si_status launch_attention(const char* stage, const AttnArgs& a, hipStrea
   return SI_OK;
 }
 
-// Matrix-core attention (bf16, head dimension 64): v is first copied with keys contiguous.
-static si_status launch_attention_mfma(const char* stage, const bf16* q, int64_t ldq, const bf16* k, int64_t ldk,
-                                       const bf16* vt, bf16* o, int64_t ldo, int S, int Nq, int Nk, int Nkp, int heads,
-                                       int kv_div, hipStream_t st, int o_frag = 0) {
+// Matrix-core attention on fragment operands (k_attn_mfma.h) of S query sequences; kv_div consecutive
+// ones share a key sequence.
+static si_status launch_attention_mfma(const char* stage, const bf16* q, const bf16* kv, bf16* o, int64_t ldo, int S, int Nq, int Nk,
+                                       int heads, int d, int kv_div, hipStream_t st, int o_frag) {
   if (S <= 0 || Nq <= 0) return SI_OK;
   StageScope scope(stage, st);
   AttnMfmaArgs a;
-  a.q = q; a.ldq = ldq; a.k = k; a.ldk = ldk; a.vt = vt; a.o = o; a.ldo = ldo;
-  a.Nq = Nq; a.Nk = Nk; a.Nkp = Nkp; a.heads = heads; a.kv_div = kv_div;
+  a.q = q; a.kv = kv; a.o = o; a.ldo = ldo;
+  a.Nq = Nq; a.Nk = Nk; a.heads = heads; a.d = d; a.kv_div = kv_div;
   a.o_frag = o_frag;
   a.ksplit = 1; a.o2 = nullptr; a.ml = nullptr; a.tiles32 = 0;
-  // 8 wavefronts share the key / value stages when that still leaves several workgroups for every CU
-  const int64_t wg8 = (int64_t)((Nq + 255) / 256) * heads * S;
-  if (wg8 >= 1024) {
-    a.nqt = (Nq + 255) / 256;
-    a.ntiles = a.nqt * heads * S;
-    attn_mfma_kernel<8><<<(unsigned)((a.ntiles + 7) / 8 * 8), 512, 0, st>>>(a);
-  } else {
-    a.nqt = (Nq + 127) / 128;
-    a.ntiles = a.nqt * heads * S;
-    attn_mfma_kernel<4><<<(unsigned)((a.ntiles + 7) / 8 * 8), 256, 0, st>>>(a);
-  }
-  SI_CHECK_LAUNCH();
-  return SI_OK;
-}
-static si_status launch_transpose_v(const char* stage, const bf16* src, int64_t ld, int col0, bf16* dst, int S, int N, int Nkp,
-                                    int D, hipStream_t st) {
-  if (S <= 0 || N <= 0) return SI_OK;
-  StageScope scope(stage, st);
-  dim3 grid((unsigned)((Nkp + 31) / 32), (unsigned)((D + 31) / 32), (unsigned)S);
-  transpose_v_kernel<<<grid, 256, 0, st>>>(src, ld, col0, dst, N, Nkp, D);
+  a.nqt = (Nq + 127) / 128;
+  a.ntiles = a.nqt * heads * S;
+  attn_dispatch(d, [&](auto ks, auto db) {
+    attn_mfma_kernel<ks.value, db.value><<<(unsigned)((a.ntiles + 7) / 8 * 8), 256, 0, st>>>(a);
+  });
   SI_CHECK_LAUNCH();
   return SI_OK;
 }
@@ -669,10 +684,11 @@ static si_status run_block(const Plan& p, const si_tensor5* x, const si_block_we
   const bool spatial = p.kind == SI_BLOCK_SPATIAL;
   const bool fused_ffn = p.fused_nb > 0, fused_attn = p.fused_attn;
   constexpr bool kF16 = sizeof(T) == 2;  // proj_in / proj_out run on fp16 operands for 16-bit storage
-  // operand buffers in fragment order + ring kernel; the attention outputs too where the matrix-core
+  // operand buffers in fragment order + ring kernel; the attention outputs too where a matrix-core
   // attention kernel writes them and a staged GEMM (not the FFN-half kernel) reads them
   const bool ring = p.ring;
-  const bool self_frag = ring && p.attn_mfma && !p.post_fused, cross_frag = ring && p.attn_mfma && !fused_ffn;
+  const bool self_frag = ring && !p.post_fused && (p.attn_mfma || (p.kind == SI_BLOCK_TEMPORAL && p.F <= 32 && !fused_ffn));
+  const bool cross_frag = ring && p.attn_mfma && !fused_ffn;
   const RingDims Mx{p.Mmax, p.lanes};
   auto cT = [](const void* q) { return static_cast<const T*>(q); };
 
@@ -725,8 +741,13 @@ static si_status run_block(const Plan& p, const si_tensor5* x, const si_block_we
         pack_ctx_stream_kernel<10><<<wgs, 256, 0, st>>>(ctxkv, p.B, p.Mc, reinterpret_cast<u32x4_t*>(ws + p.off_ffn_stream), pitch,
                                                         n_main);
         SI_CHECK_LAUNCH();
-      } else if (p.attn_mfma)
-        SI_TRY(launch_transpose_v("ctx_vt", ctxkv, (int64_t)2 * D, D, reinterpret_cast<bf16*>(ws + p.off_ctxvt), p.B, p.Mc, p.Mcp, D, st));
+      } else {
+        StageScope scope("ctx_frags", st);
+        const int64_t granules = (int64_t)(attn_kv_bytes(p.B, p.heads, p.Mc, p.d) / 16);
+        pack_ctx_frag_kernel<<<(unsigned)((granules + 255) / 256), 256, 0, st>>>(ctxkv, reinterpret_cast<u32x4_t*>(ws + p.off_ctxfrag),
+                                                                                 p.B, p.Mc, p.heads, p.d);
+        SI_CHECK_LAUNCH();
+      }
     }
   }
 
@@ -755,8 +776,8 @@ static si_status run_block(const Plan& p, const si_tensor5* x, const si_block_we
     T* a = reinterpret_cast<T*>(reinterpret_cast<char*>(a_base) + lane_off);
     float* h = reinterpret_cast<float*>(reinterpret_cast<char*>(h_base) + lane_off);
     T* big = reinterpret_cast<T*>(reinterpret_cast<char*>(big_base) + lane_off);
-    char* const vt_lane = ws + p.off_vt + lane_off;
-    (void)vt_lane;
+    char* const ml_lane = ws + p.off_ml + lane_off;
+    (void)ml_lane;
     Window win;
     win.B = p.B; win.C = C; win.F = p.F; win.P = p.P; win.G = p.G;
     if (p.axis == SI_AXIS_F) {
@@ -808,20 +829,20 @@ static si_status run_block(const Plan& p, const si_tensor5* x, const si_block_we
         {  // operands and output as fragments (q: M*D values at big, k / v^T stage blocks behind them)
           StageScope scope("self_attn", st);
           AttnMfmaArgs aa;
-          aa.q = big; aa.ldq = 0; aa.k = big + M * D; aa.ldk = 0; aa.vt = nullptr; aa.o = a; aa.ldo = 0;
-          aa.Nq = aa.Nk = aa.Nkp = win.Pw; aa.heads = p.heads; aa.kv_div = 1; aa.o_frag = 0;
+          aa.q = big; aa.kv = big + M * D; aa.o = a; aa.ldo = 0;
+          aa.Nq = aa.Nk = win.Pw; aa.heads = p.heads; aa.d = p.d; aa.kv_div = 1; aa.o_frag = 0;
           aa.nqt = win.Pw / 128;
           // two key halves per query tile when one workgroup per tile would leave the last round of
-          // workgroups (2 per CU) less than half full; the halves' statistics live in the (otherwise
-          // unused) transposed-value buffer, the second half's output behind q, k, v
+          // workgroups (2 per CU) less than half full; the halves' statistics have a buffer
+          // of their own, the second half's output lies behind q, k, v
           const int64_t wgs1 = (int64_t)aa.nqt * p.heads * p.B * win.Fw;
           aa.ksplit = (win.Pw % 256 == 0 && wgs1 > 512 && wgs1 % 512 > 0 && wgs1 % 512 <= 256) ? 2 : 1;
           ksplit = aa.ksplit;
           aa.o2 = big + 3 * M * D;
-          aa.ml = reinterpret_cast<float2*>(vt_lane);
+          aa.ml = reinterpret_cast<float2*>(ml_lane);
           aa.tiles32 = M / 32;
           aa.ntiles = (int)(wgs1 * aa.ksplit);
-          attn_mfma_kernel<4, true><<<(unsigned)((aa.ntiles + 7) / 8 * 8), 256, 0, st>>>(aa);
+          attn_mfma_kernel<4, 2, true><<<(unsigned)((aa.ntiles + 7) / 8 * 8), 256, 0, st>>>(aa);
           SI_CHECK_LAUNCH();
         }
       }
@@ -844,12 +865,16 @@ static si_status run_block(const Plan& p, const si_tensor5* x, const si_block_we
       SI_TRY(launch_layer_norm<T>("ln1", h, a, M, D, w->ln1_g, w->ln1_b, w->ln_eps, pe, win.Pw, win.Fw, win.f0, st, ring));
       bool self_done = false;
       if constexpr (sizeof(T) == 2) {
-        if (p.attn_mfma) {  // spatial: sequence (b, f) = rows (b*Fw + f)*Pw + i; the projection writes V transposed
-          bf16* vt = reinterpret_cast<bf16*>(vt_lane);
-          EpiStoreQKVt epi{big, (int64_t)3 * D, vt, D, win.Pw, qscale2};
+        if (p.attn_mfma) {  // spatial: sequence (b, f) = rows (b*Fw + f)*Pw + i; q, then k / v^T leave as fragments
+          const int S = p.B * win.Fw;
+          bf16* const kv = reinterpret_cast<bf16*>(reinterpret_cast<char*>(big) + attn_q_bytes(S, p.heads, win.Pw, p.d));
+          const AttnFragMap map{p.heads, p.d, (win.Pw + 31) / 32};
+          // value column tiles with swapped operands: whole 32-token blocks per sequence, and no tile that
+          // holds keys and values
+          const bool swap = ring && win.Pw % 32 == 0 && (2 * D) % (32 * ring_shape(Mx, 3 * D, D).tn) == 0;
+          EpiQKVFrag epi{big, kv, map, D, win.Pw, qscale2, swap ? 2 * D : 1 << 30};
           SI_TRY((launch_gemm_sel<T, false>("qkv", ring, a, (int64_t)D, wqkv, M, Mx, 3 * D, D, epi, st)));
-          SI_TRY(launch_attention_mfma("self_attn", big, (int64_t)3 * D, big + D, (int64_t)3 * D, vt, a, (int64_t)D, p.B * win.Fw,
-                                       win.Pw, win.Pw, win.Pw, p.heads, 1, st, self_frag ? D : 0));
+          SI_TRY(launch_attention_mfma("self_attn", big, kv, a, (int64_t)D, S, win.Pw, win.Pw, p.heads, p.d, 1, st, self_frag ? D : 0));
           self_done = true;
         }
       }
@@ -870,7 +895,7 @@ static si_status run_block(const Plan& p, const si_tensor5* x, const si_block_we
           at.qmap = SeqMap{win.Pw, (int64_t)p.F * win.Pw, 1, (int64_t)win.Pw};
         }
         at.kmap = at.qmap;
-        SI_TRY(launch_attention<T>("self_attn", at, st));
+        SI_TRY(launch_attention<T>("self_attn", at, st, self_frag ? D : 0));
       }
       if ((spatial || !fused_ffn) && !p.post_fused) {  // otherwise the FFN-half kernel applies W_o itself
         EpiResidual<T> epi{h, (int64_t)D, cT(w->bo), 1, nullptr};
@@ -878,20 +903,14 @@ static si_status run_block(const Plan& p, const si_tensor5* x, const si_block_we
       }
       if (spatial && !p.post_fused) {
         SI_TRY(launch_layer_norm<T>("ln2", h, a, M, D, w->ln2_g, w->ln2_b, w->ln_eps, nullptr, win.Pw, win.Fw, win.f0, st, ring));
-        {
-          EpiStore<T> epi{big, (int64_t)D, nullptr, p.attn_mfma ? qscale2 : 1.f};
+        if constexpr (sizeof(T) == 2) {  // keys / values: the context rows of the batch entry, shared by its frames
+          EpiQFrag epi{big, AttnFragMap{p.heads, p.d, (win.Pw + 31) / 32}, win.Pw, qscale2};
           SI_TRY((launch_gemm_sel<T, false>("q2", ring, a, (int64_t)D, wq2, M, Mx, D, D, epi, st)));
-        }
-        bool cross_done = false;
-        if constexpr (sizeof(T) == 2) {
-          if (p.attn_mfma) {  // keys / values: the context rows of the batch entry, shared by its frames
-            SI_TRY(launch_attention_mfma("cross_attn", big, (int64_t)D, ctxkv, (int64_t)2 * D,
-                                         reinterpret_cast<const bf16*>(ws + p.off_ctxvt), a, (int64_t)D, p.B * win.Fw, win.Pw,
-                                         p.Mc, p.Mcp, p.heads, win.Fw, st, cross_frag ? D : 0));
-            cross_done = true;
-          }
-        }
-        if (!cross_done) {
+          SI_TRY(launch_attention_mfma("cross_attn", big, reinterpret_cast<const bf16*>(ws + p.off_ctxfrag), a, (int64_t)D, p.B * win.Fw,
+                                       win.Pw, p.Mc, p.heads, p.d, win.Fw, st, cross_frag ? D : 0));
+        } else {
+          EpiStore<T> epi{big, (int64_t)D, nullptr};
+          SI_TRY((launch_gemm_sel<T, false>("q2", ring, a, (int64_t)D, wq2, M, Mx, D, D, epi, st)));
           AttnArgs at;
           at.q = big; at.k = ctxkv; at.v = ctxkv + D; at.o = a;
           at.ldq = D; at.ldk = at.ldv = (int64_t)2 * D; at.ldo = D;
@@ -927,7 +946,7 @@ static si_status run_block(const Plan& p, const si_tensor5* x, const si_block_we
           fa.Mc = p.Mc; fa.tokens_per_batch = (int)(win.Fw * win.Pw); fa.qscale = qscale2;
           fa.h_tiled = 1;
           if (ksplit == 2) {
-            fa.o2 = big + 3 * M * D; fa.ml = reinterpret_cast<const float2*>(vt_lane); fa.tiles32 = M / 32;
+            fa.o2 = big + 3 * M * D; fa.ml = reinterpret_cast<const float2*>(ml_lane); fa.tiles32 = M / 32;
           }
           ffn_half_kernel<10, true><<<blocks, 256, 0, st>>>(fa);
         } else if (p.fused_nb == 2) ffn_half_kernel<2><<<blocks, 256, 0, st>>>(fa);
