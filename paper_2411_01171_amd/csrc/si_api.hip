@@ -13,6 +13,7 @@
 #include <vector>
 
 #include "k_attn.h"
+#include "k_block_f32.h"
 #include "k_cosine.h"
 #include "k_fused.h"
 #include "k_fused_attn.h"
@@ -132,6 +133,7 @@ struct Plan {
   bool post_fused;  // spatial: everything behind the self-attention (its out-projection, LN2, query projection,
                     // attention over the context, FFN half) in one register-resident kernel
   bool attn_mfma;   // spatial, bf16: matrix-core attention on fragment operands
+  int f32_cols;     // > 0: fp32 temporal block in one kernel, tokens per workgroup
   bool ring;        // staged bf16 GEMMs run on the fragment-order ring kernel (operands in fragment order)
   int lanes;        // slices in flight (many small slices: 2 or 3, each on a stream of its own)
   size_t lane_stride;  // bytes between two lanes' slice intermediates
@@ -218,6 +220,16 @@ static si_status make_plan(const si_tensor5* x, const si_block_weights* w, const
                   p->Mc <= 32 * kCrossTiles;
   // context keys / values as the attention kernel's fragments (the post-attention kernel has its own form)
   p->off_ctxfrag = take(p->attn_mfma && !p->post_fused ? attn_kv_bytes(p->B, p->heads, p->Mc, p->d) : 0);
+  // fp32 temporal blocks whose sequences and operands fit a workgroup's LDS take the one-kernel form.  The staged
+  // kernels remain better only where large windows of wide blocks leave many token columns empty (8000 tokens in one
+  // window, D = 320, 10 frames in 16 columns: 777 us against 945; in windows of 512 tokens 1732 against 230)
+  p->f32_cols = 0;
+  if (p->dtype == SI_F32 && p->kind == SI_BLOCK_TEMPORAL && p->F <= 32 && p->C % 16 == 0 && D % 16 == 0) {
+    const int cols = p->F <= 16 ? 16 : 32;
+    const bool filled = cols / p->F * p->F * 4 >= cols * 3;
+    if (block_f32_rows(p->C, p->D, p->heads, p->F) * cols <= kF32LdsFloats && (D <= 128 || filled || p->Mmax <= 4096))
+      p->f32_cols = cols;
+  }
   // Ring GEMMs: 16-bit storage, every contraction length a multiple of the 32-wide k-tile, operand
   // buffers addressable with 32-bit byte offsets.
   p->ring = p->dtype == SI_BF16 && p->C % 32 == 0 && D % 32 == 0 &&
@@ -660,6 +672,34 @@ static si_status launch_gn_stats(const Plan& p, const T* X, const T* key, float 
   return SI_OK;
 }
 
+// The fp32 temporal block as one kernel: a launch covers every window (no intermediates outside LDS).
+static si_status run_block_f32(const Plan& p, const float* X, const si_block_weights* w, float* OUT, const float* stats,
+                               const float* pe, hipStream_t st) {
+  StageScope scope("temporal_block_f32", st);
+  auto c = [](const void* q) { return static_cast<const float*>(q); };
+  BlockF32Args a;
+  a.x = X; a.out = OUT; a.stats = stats;
+  a.gn_g = c(w->gn_g); a.gn_b = c(w->gn_b); a.w_in = c(w->w_in); a.b_in = c(w->b_in); a.ln1_g = c(w->ln1_g); a.ln1_b = c(w->ln1_b);
+  a.wq = c(w->wq); a.wk = c(w->wk); a.wv = c(w->wv); a.wo = c(w->wo); a.bo = c(w->bo); a.ln3_g = c(w->ln3_g); a.ln3_b = c(w->ln3_b);
+  a.w1 = c(w->w1); a.b1 = c(w->b1); a.w2 = c(w->w2); a.b2 = c(w->b2); a.w_out = c(w->w_out); a.b_out = c(w->b_out);
+  a.pe = pe;
+  a.B = p.B; a.C = p.C; a.F = p.F; a.G = p.G; a.heads = p.heads; a.d = p.d; a.D = p.D; a.P = p.P;
+  a.nseq = p.f32_cols / p.F;
+  a.groups = ((int64_t)p.B * p.P + a.nseq - 1) / a.nseq;
+  a.ln_eps = w->ln_eps; a.scale = 1.0f / sqrtf((float)p.d);
+  const unsigned grid = (unsigned)((a.groups + 7) / 8 * 8);
+  auto launch = [&](auto tt) {
+    if (block_f32_rows(p.C, p.D, p.heads, p.F) * p.f32_cols <= kF32SmallFloats)
+      temporal_block_f32_kernel<tt.value, kF32SmallFloats, kF32SmallThreads><<<grid, kF32SmallThreads, 0, st>>>(a);
+    else
+      temporal_block_f32_kernel<tt.value, kF32LdsFloats, kF32Threads><<<grid, kF32Threads, 0, st>>>(a);
+  };
+  if (p.f32_cols == 16) launch(std::integral_constant<int, 1>());
+  else launch(std::integral_constant<int, 2>());
+  SI_CHECK_LAUNCH();
+  return SI_OK;
+}
+
 template <typename T>
 static si_status run_block(const Plan& p, const si_tensor5* x, const si_block_weights* w, const si_context* ctx,
                            si_tensor5* out, char* ws, hipStream_t st, bool stats_done = false, bool packed = false) {
@@ -700,7 +740,7 @@ static si_status run_block(const Plan& p, const si_tensor5* x, const si_block_we
     pb.n = 0;
     pb.blocks = 0;
     PackBatch* const pbp = &pb;
-    if (!fused_attn && !p.post_fused) {
+    if (!fused_attn && !p.post_fused && !p.f32_cols) {
       SI_TRY(pack_weight<T>(cT(w->w_in), w_in, C, D, D, 0, D, 0, ring, Mx, kF16, st, pbp));
       SI_TRY(pack_weight<T>(cT(w->wq), wqkv, D, D, D, 0, 3 * D, 0, ring, Mx, false, st, pbp));
       SI_TRY(pack_weight<T>(cT(w->wk), wqkv, D, D, D, 0, 3 * D, D, ring, Mx, false, st, pbp));
@@ -714,11 +754,11 @@ static si_status run_block(const Plan& p, const si_tensor5* x, const si_block_we
       SI_TRY(launch_pack<T>(cT(w->wv2), wkv2 + (size_t)D * p.Cc, p.Cc, D, D, 0, 0, st, 0, false, 0, 0, pbp));
       if (!fused_ffn) SI_TRY(pack_weight<T>(cT(w->wo2), wo2, D, D, D, 0, D, 0, cross_frag, Mx, false, st, pbp));
     }
-    if (!fused_ffn) {
+    if (!fused_ffn && !p.f32_cols) {
       SI_TRY(pack_weight<T>(cT(w->w_out), w_out, D, C, C, 0, C, 0, ring, Mx, kF16, st, pbp));
       SI_TRY(pack_weight<T>(cT(w->w1), w1, D, 8 * D, 8 * D, 4 * D, 8 * D, 0, ring, Mx, false, st, pbp));
       SI_TRY(pack_weight<T>(cT(w->w2), w2, 4 * D, D, D, 0, D, 0, ring, Mx, false, st, pbp));
-    } else if constexpr (sizeof(T) == 2) {
+    } else if constexpr (sizeof(T) == 2) {  // fp32 in one kernel: nothing to re-lay out
       if (p.fused_nb == 2) SI_TRY(pack_fused_streams<2>(p, w, ws, pe, st));
       else SI_TRY(pack_fused_streams<10>(p, w, ws, pe, st));
     }
@@ -729,6 +769,9 @@ static si_status run_block(const Plan& p, const si_tensor5* x, const si_block_we
     }
   }
   if (!stats_done) SI_TRY(launch_gn_stats<T>(p, X, nullptr, w->gn_eps, ws, st));
+  if constexpr (sizeof(T) == 4) {
+    if (p.f32_cols) return run_block_f32(p, X, w, OUT, stats, pe, st);
+  }
   if (spatial) {
     EpiStore<T> epi{ctxkv, (int64_t)2 * D, nullptr};
     SI_TRY(launch_gemm<T>("ctx_kv", cT(ctx->ptr), (int64_t)p.Cc, wkv2, (int64_t)p.B * p.Mc, 2 * D, p.Cc, epi, st));
@@ -1000,7 +1043,7 @@ static uint64_t pack_fingerprint(const Plan& p, const si_block_weights* w) {
   int dev = -1;
   (void)hipGetDevice(&dev);
   const int64_t f[] = {p.kind, p.dtype, p.B, p.C, p.F, p.H, p.W, p.G, p.heads, p.d, p.Mc, p.Cc, p.axis, p.extent, p.slice_len,
-                       p.Mmax, p.pe, p.fused_nb, p.fused_attn, p.attn_split, p.post_fused, p.attn_mfma, p.ring, p.lanes, (int64_t)p.weights_bytes,
+                       p.Mmax, p.pe, p.fused_nb, p.fused_attn, p.attn_split, p.post_fused, p.attn_mfma, p.f32_cols, p.ring, p.lanes, (int64_t)p.weights_bytes,
                        (int64_t)p.total_bytes, (int64_t)p.off_w_in, (int64_t)p.off_ffn_stream, (int64_t)p.off_attn_stream, dev};
   uint64_t h = fnv1a(14695981039346656037ull, f, sizeof(f));
   const void* q[] = {w->gn_g, w->gn_b, w->w_in, w->b_in, w->ln1_g, w->ln1_b, w->wq, w->wk, w->wv, w->wo, w->bo,
