@@ -378,6 +378,7 @@ __global__ __launch_bounds__(WS ? 512 : 256, (WS && TM * TN > 2) ? 1 : 2) void r
 // h[m, n] = fp16(acc + bias[n] + e[b(m), n])   (token-major; e may be NULL); b(m) = m / tokens_per_batch
 struct EpiConvEmb {
   static constexpr bool kRows8 = false;
+  static constexpr bool kUp = false;
   _Float16* h;
   int64_t ld;
   const bf16* bias;
@@ -398,6 +399,7 @@ struct EpiConvEmb {
 // covers 32 consecutive granules.
 struct EpiConvEmbFrag {
   static constexpr bool kRows8 = false;
+  static constexpr bool kUp = false;
   _Float16* h;
   int C;
   const bf16* bias;
@@ -418,6 +420,7 @@ struct EpiConvEmbFrag {
 // 16-byte accesses when the eight tokens are eight aligned positions of one image.
 struct EpiSliceOutRows {
   static constexpr bool kRows8 = true;
+  static constexpr bool kUp = false;
   const bf16* x;
   bf16* out;
   const bf16* bias;
@@ -458,6 +461,7 @@ struct EpiSliceOutRows {
 // resampling operators' output.  Same addressing as EpiSliceOutRows, w describes the OUTPUT tensor.
 struct EpiStoreRows {
   static constexpr bool kRows8 = true;
+  static constexpr bool kUp = true;  // conv_halo_kernel with this epilogue: source map doubled
   bf16* out;
   const bf16* bias;
   Window w;

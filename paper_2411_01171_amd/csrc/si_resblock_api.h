@@ -2,7 +2,7 @@
 // workspace layout, the slice loop over frame windows and the kernel launches.  Part of the
 // translation unit si_api.hip (uses its stage timing, alignment and overlap helpers).
 #pragma once
-#include "k_conv.h"
+#include "k_conv_halo.h"
 
 #ifndef SI_RES_LANES3_MIN
 #define SI_RES_LANES3_MIN 12
@@ -18,6 +18,7 @@ struct ResPlan {
   int Co;              // output channels (== C: identity skip, else the 1x1 skip convolution runs)
   int TN, ncol;        // column tiles of the convolution kernel: ncol tiles of TN*32 output channels
   int64_t P, slice_len, Mmax;
+  int halo;            // > 0: the convolutions run on conv_halo_kernel, with that many 64-token blocks per patch
   int lanes;           // frame windows in flight (two streams) when there are many small ones
   size_t lane_stride;
   size_t off_stats, off_emb, off_a, off_xr, off_h, off_stats2, off_part, off_w1, off_w2, off_wskip;
@@ -25,6 +26,7 @@ struct ResPlan {
 };
 
 static void conv_column_tiles(int O, int64_t rows_in_flight, int* TN, int* ncol);
+static int halo_plan(int B, int F, int O, int H, int W, int Wi, int mode);
 
 static si_status make_res_plan(const si_tensor5* x, const si_resblock_weights* w, int64_t slice_len, ResPlan* p) {
   if (!x || !w) return SI_ERR_NULL;
@@ -72,7 +74,11 @@ static si_status make_res_plan(const si_tensor5* x, const si_resblock_weights* w
   p->lane_stride = off - p->off_a;
   for (int l = 1; l < p->lanes; ++l) take(p->lane_stride);
   const size_t act_end = off;
-  conv_column_tiles(p->Co, (p->Mmax + 127) / 128 * p->lanes, &p->TN, &p->ncol);
+  p->halo = halo_plan(p->B, p->F, p->Co, p->H, p->W, p->W, kConvSame);
+  if (p->halo) {
+    p->TN = kHaloTN;
+    p->ncol = p->Co / (32 * kHaloTN);
+  } else conv_column_tiles(p->Co, (p->Mmax + 127) / 128 * p->lanes, &p->TN, &p->ncol);
   const size_t per_ktile = (size_t)p->ncol * 2 * p->TN * 1024;  // bytes of one 32-channel k-tile over all column tiles
   p->off_w1 = take(per_ktile * 9 * (C / 32));
   p->off_w2 = take(per_ktile * 9 * (Co / 32));
@@ -114,14 +120,35 @@ static void conv_column_tiles(int O, int64_t rows_in_flight, int* TN, int* ncol)
   }
 }
 
-// Row tiles of 256 tokens when that still gives every CU two blocks, else 128 tokens.  M output
+// Whether a 3x3 convolution of O output channels on H x W maps runs on conv_halo_kernel: its patch size in 64-token
+// blocks, else 0.  A function of the whole call, not of the window, so that every slicing runs the same kernel and
+// gives the same bits.  tiles: workgroups of one frame of all batch entries; eight or more frames are at least two of
+// those in flight, as one window of two frames or as two windows.  Measured (ring kernel -> this one, calls of one frame
+// per window): 64 tiles x 2 in flight 606 -> 563 us (320 channels, 64 x 64, 8 frames) and 716 -> 573 us (1280
+// channels doubled to 32 x 32); 36 x 2: 864 -> 1130 us, 40 x 2: 1049 -> 1272 us, 72 x 1: 887 -> 1099 us: half of the
+// 256 CUs have to have a workgroup.  Maps wider than the patch buffer stay on the ring kernel too.
+constexpr int kHaloMin = 128, kHaloMaxBlocks = 12;
+static int halo_plan(int B, int F, int O, int H, int W, int Wi, int mode) {
+  const int64_t tiles = ((int64_t)B * H * W + kHaloTokens - 1) / kHaloTokens * (O / (32 * kHaloTN)), nblk = halo_blocks(W, Wi, mode);
+  return O % (32 * kHaloTN) == 0 && tiles * (F >= 8 ? 2 : 1) >= kHaloMin && nblk <= kHaloMaxBlocks ? (int)nblk : 0;
+}
+
+// halo_nblk > 0: conv_halo_kernel.  Else row tiles of 256 tokens when that still gives every CU two blocks, or of 128.  M output
 // tokens on an H x W map; (Hi, Wi, mode) describe the source map (see ConvArgs).
 template <bool F16, class Epi>
 static si_status launch_conv3x3(const char* stage, const void* act, const void* wf, int64_t M, int C, int TN, int ncol, int H,
-                                int W, int Hi, int Wi, int mode, Epi epi, hipStream_t st, int O = 0, int ntaps = 9) {
+                                int W, int Hi, int Wi, int mode, Epi epi, hipStream_t st, int O = 0, int ntaps = 9, int halo_nblk = 0) {
   StageScope scope(stage, st);
   ConvArgs a{static_cast<const char*>(act), static_cast<const char*>(wf), M, C, O ? O : C, H, W, ncol, 0, Hi, Wi, mode, ntaps};
   const int64_t rows2 = (M + 255) / 256;
+  if (halo_nblk) {
+    a.ntiles = (int)((M + kHaloTokens - 1) / kHaloTokens * ncol);
+    const unsigned grid = (unsigned)((a.ntiles + 7) / 8 * 8);
+    if (halo_nblk <= 9) conv_halo_kernel<9, F16, Epi::kUp><<<grid, 512, 0, st>>>(a, halo_nblk, epi);
+    else conv_halo_kernel<kHaloMaxBlocks, F16, Epi::kUp><<<grid, 512, 0, st>>>(a, halo_nblk, epi);
+    SI_CHECK_LAUNCH();
+    return SI_OK;
+  }
   const bool big = rows2 * ncol >= SI_CONV_BIG_MIN;
   a.ntiles = (int)((big ? rows2 : (M + 127) / 128) * ncol);
   switch (TN * 2 + (big ? 1 : 0)) {
@@ -229,10 +256,10 @@ static si_status run_resblock(const ResPlan& p, const si_tensor5* x, const si_re
     const bool frag_h = p.P % 32 == 0;
     if (frag_h) {
       EpiConvEmbFrag epi{h, Co, cB(w->b_conv1), emb, (int64_t)Fw * p.P};
-      SI_TRY(launch_conv3x3<true>("conv1", a, w1, M, C, p.TN, p.ncol, p.H, p.W, p.H, p.W, kConvSame, epi, st, Co));
+      SI_TRY(launch_conv3x3<true>("conv1", a, w1, M, C, p.TN, p.ncol, p.H, p.W, p.H, p.W, kConvSame, epi, st, Co, 9, p.halo));
     } else {
       EpiConvEmb epi{h, (int64_t)Co, cB(w->b_conv1), emb, (int64_t)Fw * p.P};
-      SI_TRY(launch_conv3x3<true>("conv1", a, w1, M, C, p.TN, p.ncol, p.H, p.W, p.H, p.W, kConvSame, epi, st, Co));
+      SI_TRY(launch_conv3x3<true>("conv1", a, w1, M, C, p.TN, p.ncol, p.H, p.W, p.H, p.W, kConvSame, epi, st, Co, 9, p.halo));
     }
     {
       StageScope scope("gn2_stats", st);
@@ -266,7 +293,7 @@ static si_status run_resblock(const ResPlan& p, const si_tensor5* x, const si_re
     {
       // residual source: x itself, or the skip convolution's result already sitting in the out window
       EpiSliceOutRows epi{skip_conv ? OUT : X, OUT, cB(w->b_conv2), win_out};
-      SI_TRY(launch_conv3x3<true>("conv2", frag_h ? h : a, w2, M, Co, p.TN, p.ncol, p.H, p.W, p.H, p.W, kConvSame, epi, st));
+      SI_TRY(launch_conv3x3<true>("conv2", frag_h ? h : a, w2, M, Co, p.TN, p.ncol, p.H, p.W, p.H, p.W, kConvSame, epi, st, Co, 9, p.halo));
     }
   }
   if (lanes >= 2) SI_TRY(lanes_join(aux, lanes, st0));
@@ -276,7 +303,7 @@ static si_status run_resblock(const ResPlan& p, const si_tensor5* x, const si_re
 // ----------------------------------------------------------------------------- Up/DownSample
 
 struct ResamplePlan {
-  int B, C, F, Hi, Wi, Ho, Wo, mode, TN, ncol;
+  int B, C, F, Hi, Wi, Ho, Wo, mode, TN, ncol, halo;
   int64_t Pi, Po, slice_len, Mi_max;
   int lanes;
   size_t lane_stride, off_a, off_w, weights_bytes, total_bytes;
@@ -302,7 +329,11 @@ static si_status make_resample_plan(const si_tensor5* x, int32_t kind, int64_t s
   if ((int64_t)p->B * p->slice_len * p->Po >= (1LL << 31) / 16) return SI_ERR_SHAPE;
   const int64_t n_slices = (p->F + p->slice_len - 1) / p->slice_len;
   p->lanes = n_slices >= 8 ? 2 : 1;
-  conv_column_tiles(p->C, ((int64_t)p->B * p->slice_len * p->Po + 127) / 128 * p->lanes, &p->TN, &p->ncol);
+  p->halo = p->mode == kConvNearestUp ? halo_plan(p->B, p->F, p->C, p->Ho, p->Wo, p->Wi, p->mode) : 0;
+  if (p->halo) {
+    p->TN = kHaloTN;
+    p->ncol = p->C / (32 * kHaloTN);
+  } else conv_column_tiles(p->C, ((int64_t)p->B * p->slice_len * p->Po + 127) / 128 * p->lanes, &p->TN, &p->ncol);
   size_t off = 0;
   auto take = [&](size_t bytes) {
     const size_t o = off;
@@ -355,7 +386,7 @@ static si_status run_resample(const ResamplePlan& p, const si_tensor5* x, const 
     }
     EpiStoreRows epi{OUT, static_cast<const bf16*>(b_conv), win_out};
     SI_TRY(launch_conv3x3<false>(p.mode == kConvStride2 ? "conv_down" : "conv_up", a, wf, (int64_t)p.B * Fw * p.Po, C, p.TN,
-                                 p.ncol, p.Ho, p.Wo, p.Hi, p.Wi, p.mode, epi, st));
+                                 p.ncol, p.Ho, p.Wo, p.Hi, p.Wi, p.mode, epi, st, 0, 9, p.halo));
   }
   if (lanes == 2) SI_TRY(lanes_join(aux, lanes, st0));
   return SI_OK;
