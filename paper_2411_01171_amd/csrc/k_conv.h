@@ -84,13 +84,6 @@ struct epi_block32 : std::false_type {};
 template <class Epi>
 struct epi_block32<Epi, std::enable_if_t<Epi::kBlock32>> : std::true_type {};
 
-// An epilogue with kSwapCols takes the column tiles at or behind its swap_from transposed: the operands
-// change places, a lane ends up with 16 tokens of one output channel.
-template <class Epi, class = void>
-struct epi_swaps : std::false_type {};
-template <class Epi>
-struct epi_swaps<Epi, std::enable_if_t<Epi::kSwapCols>> : std::true_type {};
-
 template <int TM, int TN, int STAGES, bool F16, class Epi, bool WS = false>
 __global__ __launch_bounds__(WS ? 512 : 256, (WS && TM * TN > 2) ? 1 : 2) void ring_mma_kernel(ConvArgs a, Epi epi) {
   constexpr int AF = 4 * TM * 2, WFR = 2 * TN;           // fragments per stage
@@ -190,9 +183,6 @@ __global__ __launch_bounds__(WS ? 512 : 256, (WS && TM * TN > 2) ? 1 : 2) void r
     }
   };
 
-  // k loop and epilogue, instantiated per operand order (a branch inside the loop would double the accumulators)
-  auto run = [&](auto swap_tag) {
-  constexpr bool SWAP = decltype(swap_tag)::value;
   f32x16_t acc[TN][TM];
 #pragma unroll
   for (int i = 0; i < TN; ++i)
@@ -222,10 +212,7 @@ __global__ __launch_bounds__(WS ? 512 : 256, (WS && TM * TN > 2) ? 1 : 2) void r
       for (int i = 0; i < TN; ++i)
 #pragma unroll
         for (int j = 0; j < TM; ++j) {
-          if constexpr (SWAP)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, f.af[ks][j]),
-                                                                __builtin_bit_cast(bf16x8_t, f.wf[ks][i]), acc[i][j], 0, 0, 0);
-          else if constexpr (F16)
+          if constexpr (F16)
             acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8_t, f.wf[ks][i]),
                                                                __builtin_bit_cast(f16x8_t, f.af[ks][j]), acc[i][j], 0, 0, 0);
           else
@@ -320,22 +307,6 @@ __global__ __launch_bounds__(WS ? 512 : 256, (WS && TM * TN > 2) ? 1 : 2) void r
   }
 
   if (producer) return;
-  if constexpr (epi_swaps<Epi>::value) {
-    if constexpr (SWAP) {
-      static_assert(!F16, "swapped tiles contract bf16 operands");
-#pragma unroll
-      for (int j = 0; j < TM; ++j) {
-        const int64_t mb = m0 + (wave * TM + j) * 32;
-        if (mb >= a.M) continue;
-#pragma unroll
-        for (int i = 0; i < TN; ++i) {
-          const int n = (col * TN + i) * 32 + trow;
-          if (n < a.O) epi.vblock32(mb, n, acc[i][j], half);
-        }
-      }
-      return;
-    }
-  }
   if constexpr (epi_block32<Epi>::value) {
     // whole 32-column blocks go to the epilogue's block form (every lane takes part in its exchange)
     if (a.O % 32 == 0) {
@@ -365,14 +336,6 @@ __global__ __launch_bounds__(WS ? 512 : 256, (WS && TM * TN > 2) ? 1 : 2) void r
       }
     }
   }
-  };
-  if constexpr (epi_swaps<Epi>::value) {
-    if (col * TN * 32 >= epi.swap_from) {
-      run(std::true_type());
-      return;
-    }
-  }
-  run(std::false_type());
 }
 
 // h[m, n] = fp16(acc + bias[n] + e[b(m), n])   (token-major; e may be NULL); b(m) = m / tokens_per_batch

@@ -6,7 +6,7 @@
 // from the feature tensor: for one channel the 32 tokens of a wavefront are 64 contiguous bytes.
 // proj_in runs on fp16 operands (the normalised input is bounded; three more significand bits than
 // bf16), everything behind LN1 on bf16.  q, k and v leave as the MFMA fragments that the attention
-// kernel consumes (attn_mfma_kernel): a result block's register halves, packed to bf16, are
+// kernel consumes (attn_mfma_kernel, FRAGIN): a result block's register halves, packed to bf16, are
 // such fragments as they stand -- for v with the operands swapped (activations as the row operand),
 // which yields V^T.  Every store of a wavefront is one contiguous KiB.
 #pragma once
@@ -21,8 +21,8 @@ struct SpatialPreArgs {
   const u32x4_t* stream;  // W_in blocks (fp16), then W_q, W_k, W_v blocks: 4 * NB sub-chunks
   float* h;               // residual stream, workgroup-tile order (h_tile_index)
   u32x4_t* qf;            // q * qscale as fragments: [(sequence, head)][32-query tile][k-step 0..3][lane]
-  u32x4_t* kvf;           // k and v^T as fragments: [(sequence, head)][32-key tile][4 of k, 4 of v^T][lane]
-                          // (attn_mfma_kernel)
+  u32x4_t* kvf;           // k and v^T as fragments: [(sequence, head)][64-key stage][16][lane], the attention
+                          // kernel's stage order (attn_mfma_kernel, FRAGIN)
   int64_t M;              // tokens of the window, a multiple of 128; sequence (b, f) = rows (b*Fw + f)*Pw + i
   float ln_eps, qscale;
   Window win;             // p0 == 0, Pw == P, P % 128 == 0
@@ -175,7 +175,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   constexpr int NH = D / 64;
   const int tile = key0 / 32, tiles = w.Pw / 32;  // this wavefront's 32 tokens inside their sequence
   u32x4_t* const qdst = a.qf + ((int64_t)seq * NH * tiles + tile) * 4 * kWave + lane;
-  u32x4_t* const kvdst = a.kvf + ((int64_t)seq * NH * tiles + tile) * 8 * kWave + lane;
+  u32x4_t* const kvdst = a.kvf + (((int64_t)seq * NH * (tiles / 2) + tile / 2) * 16 + 4 * (tile % 2)) * kWave + lane;
 #pragma unroll
   for (int blk = 0; blk < 2 * NB; ++blk) {
     f32x16_t acc;
@@ -201,7 +201,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
       const u32x4_t o = __builtin_bit_cast(u32x4_t, to_operand(v));
       const int ks = 2 * (nb % 2) + hf;
       if (blk < NB) qdst[((int64_t)hd * tiles * 4 + ks) * kWave] = o;
-      else kvdst[((int64_t)hd * tiles * 8 + ks) * kWave] = o;
+      else kvdst[((int64_t)hd * (tiles / 2) * 16 + ks) * kWave] = o;
     }
   }
 
@@ -227,7 +227,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
       float v[8];
 #pragma unroll
       for (int e = 0; e < 8; ++e) v[e] = acc[8 * hf + e];
-      kvdst[((int64_t)(nb / 2) * tiles * 8 + 4 + 2 * (nb % 2) + hf) * kWave] = __builtin_bit_cast(u32x4_t, to_operand(v));
+      kvdst[((int64_t)(nb / 2) * (tiles / 2) * 16 + 8 + 2 * (nb % 2) + hf) * kWave] = __builtin_bit_cast(u32x4_t, to_operand(v));
     }
   }
 #undef SI_REFILL

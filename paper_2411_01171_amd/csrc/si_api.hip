@@ -13,6 +13,7 @@
 #include <vector>
 
 #include "k_attn.h"
+#include "k_attn_f32mma.h"
 #include "k_block_f32.h"
 #include "k_cosine.h"
 #include "k_fused.h"
@@ -132,13 +133,14 @@ struct Plan {
                     // token tiles (F leaves many of a wavefront's 32 columns empty in the one-kernel form)
   bool post_fused;  // spatial: everything behind the self-attention (its out-projection, LN2, query projection,
                     // attention over the context, FFN half) in one register-resident kernel
-  bool attn_mfma;   // spatial, bf16: matrix-core attention on fragment operands
+  bool attn_mfma;   // bf16 matrix-core attention kernel for the staged spatial path (heads of 64, H*W a multiple of 8)
   int f32_cols;     // > 0: fp32 temporal block in one kernel, tokens per workgroup
   bool ring;        // staged bf16 GEMMs run on the fragment-order ring kernel (operands in fragment order)
   int lanes;        // slices in flight (many small slices: 2 or 3, each on a stream of its own)
   size_t lane_stride;  // bytes between two lanes' slice intermediates
+  int Mcp;          // context tokens rounded up to a multiple of 8 (transposed value copy)
   // workspace offsets (bytes)
-  size_t off_stats, off_rehash, off_pe, off_ctxkv, off_ctxfrag, off_ml;
+  size_t off_stats, off_rehash, off_pe, off_ctxkv, off_ctxvt, off_ml;
   size_t off_w_in, off_wqkv, off_wo, off_wq2, off_wkv2, off_wo2, off_w1, off_w2, off_w_out;
   size_t off_a, off_h, off_big, off_ffn_stream, off_attn_stream, off_pre_stream;
   size_t weights_bytes, total_bytes;
@@ -197,7 +199,8 @@ static si_status make_plan(const si_tensor5* x, const si_block_weights* w, const
   };
   // slice-independent activation-derived items
   p->off_stats = take((size_t)p->B * p->F * p->G * 2 * sizeof(float));
-  p->attn_mfma = p->dtype == SI_BF16 && p->kind == SI_BLOCK_SPATIAL;
+  p->attn_mfma = p->dtype == SI_BF16 && p->kind == SI_BLOCK_SPATIAL && p->d == 64 && P % 8 == 0;
+  p->Mcp = (p->Mc + 7) / 8 * 8;
   // which path: register-resident kernels need bf16, C == D = 64 or 320 (instantiated widths)
   p->fused_nb = 0;
   p->fused_attn = false;
@@ -218,8 +221,8 @@ static si_status make_plan(const si_tensor5* x, const si_block_weights* w, const
   // channels (two 32-channel blocks), at most kCrossTiles key tiles
   p->post_fused = p->fused_nb == 10 && p->kind == SI_BLOCK_SPATIAL && p->attn_mfma && p->d == 64 && P % 128 == 0 &&
                   p->Mc <= 32 * kCrossTiles;
-  // context keys / values as the attention kernel's fragments (the post-attention kernel has its own form)
-  p->off_ctxfrag = take(p->attn_mfma && !p->post_fused ? attn_kv_bytes(p->B, p->heads, p->Mc, p->d) : 0);
+  // context values with keys contiguous (the post-attention kernel has its own form)
+  p->off_ctxvt = take(p->attn_mfma && !p->post_fused ? (size_t)p->B * Dz * p->Mcp * es : 0);
   // fp32 temporal blocks whose sequences and operands fit a workgroup's LDS take the one-kernel form.  The staged
   // kernels remain better only where large windows of wide blocks leave many token columns empty (8000 tokens in one
   // window, D = 320, 10 frames in 16 columns: 777 us against 945; in windows of 512 tokens 1732 against 230)
@@ -248,12 +251,7 @@ static si_status make_plan(const si_tensor5* x, const si_block_weights* w, const
     const size_t pad = p->ring ? kActZeroBytes : 0, Mp = p->ring ? (size_t)((p->Mmax + 31) / 32 * 32) : (size_t)p->Mmax;
     p->off_a = take(pad + Mp * (C > Dz ? C : Dz) * es);
     p->off_h = take((size_t)p->Mmax * Dz * sizeof(float));
-    size_t big = pad + Mp * 4 * Dz * es;
-    if (p->attn_mfma && !p->post_fused) {  // q, then k / v fragments (within 4 D per token unless H*W or d pads a lot)
-      const size_t frags = attn_q_bytes(p->B * p->slice_len, p->heads, P, p->d) + attn_kv_bytes(p->B * p->slice_len, p->heads, P, p->d);
-      big = big > frags ? big : frags;
-    }
-    p->off_big = take(big);
+    p->off_big = take(pad + Mp * 4 * Dz * es);
   }
   // post_fused: (reference maximum, row sum) of the two key halves
   p->off_ml = take(p->post_fused ? (size_t)2 * p->heads * (p->Mmax / 32) * kWave * sizeof(float2) : 0);
@@ -272,9 +270,9 @@ static si_status make_plan(const si_tensor5* x, const si_block_weights* w, const
   // when those are large enough.
   const size_t rehash_bytes = (size_t)p->B * p->F * p->G * 3 * sizeof(double) + 16;
   p->off_rehash = rehash_bytes <= p->lane_stride ? p->off_a : take(rehash_bytes);
-  // context keys / values before they are re-ordered: gone when the first window starts, likewise
+  // context keys / values; post_fused: re-ordered before the first window starts, likewise
   const size_t ctx_bytes = (size_t)p->B * p->Mc * 2 * Dz * es;
-  p->off_ctxkv = (p->attn_mfma && ctx_bytes <= p->lane_stride) ? p->off_a : take(ctx_bytes);
+  p->off_ctxkv = (p->post_fused && ctx_bytes <= p->lane_stride) ? p->off_a : take(ctx_bytes);
   const size_t act_end = off;
   // frame position table (a function of F and D only: written with the weight re-layout)
   p->off_pe = take(p->pe ? (size_t)p->F * Dz * sizeof(float) : 0);
@@ -449,7 +447,7 @@ static si_status launch_gemm_sel(const char* stage, bool as_ring, const T* A, in
 // Calls f(integral_constant<KS>, integral_constant<DB>) for head dimension d = 8 .. 128.
 template <class Fn>
 static void attn_dispatch(int d, Fn f) {
-  switch (attn_ksteps(d)) {
+  switch ((d + 15) / 16) {
     case 1: f(std::integral_constant<int, 1>(), std::integral_constant<int, 1>()); break;
     case 2: f(std::integral_constant<int, 2>(), std::integral_constant<int, 1>()); break;
     case 3: f(std::integral_constant<int, 3>(), std::integral_constant<int, 2>()); break;
@@ -461,50 +459,72 @@ static void attn_dispatch(int d, Fn f) {
   }
 }
 
-// sequences of up to 32 tokens in 16-bit storage go to the matrix cores
-template <typename T>
-static bool attention_is_short(const AttnArgs& a) {
-  return sizeof(T) == 2 && a.Nq == a.Nk && a.Nk <= 32 && a.ldq % 8 == 0 && a.ldk % 8 == 0 && a.ldv % 8 == 0 && a.ldo % 8 == 0 &&
-         aligned16(a.q) && aligned16(a.k) && aligned16(a.v) && aligned16(a.o);
+// Calls f(integral_constant<d / 8>) for head dimension d = 8 .. 128, a multiple of 8.
+template <int D8 = 1, class Fn>
+static void head_dispatch(int d, Fn f) {
+  if constexpr (D8 <= 16) {
+    if (d == 8 * D8) f(std::integral_constant<int, D8>());
+    else head_dispatch<D8 + 1>(d, f);
+  }
 }
 
+// o_frag (16-bit storage): 0, or o is a fragment-order buffer of that many channels per token.  Rows and head columns
+// of q, k and v are 16-byte pieces throughout (D and d are multiples of 8, the buffers 256-byte aligned).
 template <typename T>
 static si_status launch_attention(const char* stage, const AttnArgs& a, hipStream_t st, int o_frag = 0) {
   if (a.S <= 0 || a.Nq <= 0) return SI_OK;
   StageScope scope(stage, st);
   if constexpr (sizeof(T) == 2) {
-    if (attention_is_short<T>(a)) {
+    if (a.Nq == a.Nk && a.Nk <= 32) {  // sequences of up to 32 tokens: one wavefront per (sequence, head)
       const int64_t wgs = (int64_t)((a.S + 3) / 4) * a.heads;
       attn_dispatch(a.d, [&](auto ks, auto db) {
         attn_short_kernel<ks.value, db.value><<<(unsigned)((wgs + 7) / 8 * 8), 256, 0, st>>>(a, o_frag);
       });
-      SI_CHECK_LAUNCH();
-      return SI_OK;
+    } else {
+      const int64_t tiles = (int64_t)((a.Nq + 127) / 128) * a.heads * a.S, most = 1 << 20;  // a launch is less than 2^32 threads
+      const unsigned grid = (unsigned)(((tiles < most ? tiles : most) + 7) / 8 * 8);
+      head_dispatch(a.d, [&](auto d8) { attn_f32mma_kernel<d8.value><<<grid, 256, 0, st>>>(a, o_frag); });
     }
+  } else {
+    constexpr int QB = 4;
+    dim3 grid((unsigned)((a.Nq + 4 * QB - 1) / (4 * QB)), (unsigned)a.heads, (unsigned)a.S);
+    attn_valu_kernel<T, QB><<<grid, 256, 0, st>>>(a);
   }
-  constexpr int QB = 4;
-  dim3 grid((unsigned)((a.Nq + 4 * QB - 1) / (4 * QB)), (unsigned)a.heads, (unsigned)a.S);
-  attn_valu_kernel<T, QB><<<grid, 256, 0, st>>>(a);
   SI_CHECK_LAUNCH();
   return SI_OK;
 }
 
-// Matrix-core attention on fragment operands (k_attn_mfma.h) of S query sequences; kv_div consecutive
-// ones share a key sequence.
-static si_status launch_attention_mfma(const char* stage, const bf16* q, const bf16* kv, bf16* o, int64_t ldo, int S, int Nq, int Nk,
-                                       int heads, int d, int kv_div, hipStream_t st, int o_frag) {
+// Matrix-core attention (bf16, head dimension 64): v is first copied with keys contiguous.
+static si_status launch_attention_mfma(const char* stage, const bf16* q, int64_t ldq, const bf16* k, int64_t ldk,
+                                       const bf16* vt, bf16* o, int64_t ldo, int S, int Nq, int Nk, int Nkp, int heads,
+                                       int kv_div, hipStream_t st, int o_frag = 0) {
   if (S <= 0 || Nq <= 0) return SI_OK;
   StageScope scope(stage, st);
   AttnMfmaArgs a;
-  a.q = q; a.kv = kv; a.o = o; a.ldo = ldo;
-  a.Nq = Nq; a.Nk = Nk; a.heads = heads; a.d = d; a.kv_div = kv_div;
+  a.q = q; a.ldq = ldq; a.k = k; a.ldk = ldk; a.vt = vt; a.o = o; a.ldo = ldo;
+  a.Nq = Nq; a.Nk = Nk; a.Nkp = Nkp; a.heads = heads; a.kv_div = kv_div;
   a.o_frag = o_frag;
   a.ksplit = 1; a.o2 = nullptr; a.ml = nullptr; a.tiles32 = 0;
-  a.nqt = (Nq + 127) / 128;
-  a.ntiles = a.nqt * heads * S;
-  attn_dispatch(d, [&](auto ks, auto db) {
-    attn_mfma_kernel<ks.value, db.value><<<(unsigned)((a.ntiles + 7) / 8 * 8), 256, 0, st>>>(a);
-  });
+  // 8 wavefronts share the key / value stages when that still leaves several workgroups for every CU
+  const int64_t wg8 = (int64_t)((Nq + 255) / 256) * heads * S;
+  if (wg8 >= 1024) {
+    a.nqt = (Nq + 255) / 256;
+    a.ntiles = a.nqt * heads * S;
+    attn_mfma_kernel<8><<<(unsigned)((a.ntiles + 7) / 8 * 8), 512, 0, st>>>(a);
+  } else {
+    a.nqt = (Nq + 127) / 128;
+    a.ntiles = a.nqt * heads * S;
+    attn_mfma_kernel<4><<<(unsigned)((a.ntiles + 7) / 8 * 8), 256, 0, st>>>(a);
+  }
+  SI_CHECK_LAUNCH();
+  return SI_OK;
+}
+static si_status launch_transpose_v(const char* stage, const bf16* src, int64_t ld, int col0, bf16* dst, int S, int N, int Nkp,
+                                    int D, hipStream_t st) {
+  if (S <= 0 || N <= 0) return SI_OK;
+  StageScope scope(stage, st);
+  dim3 grid((unsigned)((Nkp + 31) / 32), (unsigned)((D + 31) / 32), (unsigned)S);
+  transpose_v_kernel<<<grid, 256, 0, st>>>(src, ld, col0, dst, N, Nkp, D);
   SI_CHECK_LAUNCH();
   return SI_OK;
 }
@@ -724,11 +744,10 @@ static si_status run_block(const Plan& p, const si_tensor5* x, const si_block_we
   const bool spatial = p.kind == SI_BLOCK_SPATIAL;
   const bool fused_ffn = p.fused_nb > 0, fused_attn = p.fused_attn;
   constexpr bool kF16 = sizeof(T) == 2;  // proj_in / proj_out run on fp16 operands for 16-bit storage
-  // operand buffers in fragment order + ring kernel; the attention outputs too where a matrix-core
-  // attention kernel writes them and a staged GEMM (not the FFN-half kernel) reads them
+  // operand buffers in fragment order + ring kernel; the attention outputs too where a staged GEMM
+  // (not the FFN-half kernel) reads them
   const bool ring = p.ring;
-  const bool self_frag = ring && !p.post_fused && (p.attn_mfma || (p.kind == SI_BLOCK_TEMPORAL && p.F <= 32 && !fused_ffn));
-  const bool cross_frag = ring && p.attn_mfma && !fused_ffn;
+  const bool self_frag = ring && !p.post_fused && (spatial || !fused_ffn), cross_frag = ring && !fused_ffn;
   const RingDims Mx{p.Mmax, p.lanes};
   auto cT = [](const void* q) { return static_cast<const T*>(q); };
 
@@ -784,13 +803,8 @@ static si_status run_block(const Plan& p, const si_tensor5* x, const si_block_we
         pack_ctx_stream_kernel<10><<<wgs, 256, 0, st>>>(ctxkv, p.B, p.Mc, reinterpret_cast<u32x4_t*>(ws + p.off_ffn_stream), pitch,
                                                         n_main);
         SI_CHECK_LAUNCH();
-      } else {
-        StageScope scope("ctx_frags", st);
-        const int64_t granules = (int64_t)(attn_kv_bytes(p.B, p.heads, p.Mc, p.d) / 16);
-        pack_ctx_frag_kernel<<<(unsigned)((granules + 255) / 256), 256, 0, st>>>(ctxkv, reinterpret_cast<u32x4_t*>(ws + p.off_ctxfrag),
-                                                                                 p.B, p.Mc, p.heads, p.d);
-        SI_CHECK_LAUNCH();
-      }
+      } else if (p.attn_mfma)
+        SI_TRY(launch_transpose_v("ctx_vt", ctxkv, (int64_t)2 * D, D, reinterpret_cast<bf16*>(ws + p.off_ctxvt), p.B, p.Mc, p.Mcp, D, st));
     }
   }
 
@@ -872,8 +886,8 @@ static si_status run_block(const Plan& p, const si_tensor5* x, const si_block_we
         {  // operands and output as fragments (q: M*D values at big, k / v^T stage blocks behind them)
           StageScope scope("self_attn", st);
           AttnMfmaArgs aa;
-          aa.q = big; aa.kv = big + M * D; aa.o = a; aa.ldo = 0;
-          aa.Nq = aa.Nk = win.Pw; aa.heads = p.heads; aa.d = p.d; aa.kv_div = 1; aa.o_frag = 0;
+          aa.q = big; aa.ldq = 0; aa.k = big + M * D; aa.ldk = 0; aa.vt = nullptr; aa.o = a; aa.ldo = 0;
+          aa.Nq = aa.Nk = aa.Nkp = win.Pw; aa.heads = p.heads; aa.kv_div = 1; aa.o_frag = 0;
           aa.nqt = win.Pw / 128;
           // two key halves per query tile when one workgroup per tile would leave the last round of
           // workgroups (2 per CU) less than half full; the halves' statistics have a buffer
@@ -885,7 +899,7 @@ static si_status run_block(const Plan& p, const si_tensor5* x, const si_block_we
           aa.ml = reinterpret_cast<float2*>(ml_lane);
           aa.tiles32 = M / 32;
           aa.ntiles = (int)(wgs1 * aa.ksplit);
-          attn_mfma_kernel<4, 2, true><<<(unsigned)((aa.ntiles + 7) / 8 * 8), 256, 0, st>>>(aa);
+          attn_mfma_kernel<4, true><<<(unsigned)((aa.ntiles + 7) / 8 * 8), 256, 0, st>>>(aa);
           SI_CHECK_LAUNCH();
         }
       }
@@ -908,16 +922,12 @@ static si_status run_block(const Plan& p, const si_tensor5* x, const si_block_we
       SI_TRY(launch_layer_norm<T>("ln1", h, a, M, D, w->ln1_g, w->ln1_b, w->ln_eps, pe, win.Pw, win.Fw, win.f0, st, ring));
       bool self_done = false;
       if constexpr (sizeof(T) == 2) {
-        if (p.attn_mfma) {  // spatial: sequence (b, f) = rows (b*Fw + f)*Pw + i; q, then k / v^T leave as fragments
-          const int S = p.B * win.Fw;
-          bf16* const kv = reinterpret_cast<bf16*>(reinterpret_cast<char*>(big) + attn_q_bytes(S, p.heads, win.Pw, p.d));
-          const AttnFragMap map{p.heads, p.d, (win.Pw + 31) / 32};
-          // value column tiles with swapped operands: whole 32-token blocks per sequence, and no tile that
-          // holds keys and values
-          const bool swap = ring && win.Pw % 32 == 0 && (2 * D) % (32 * ring_shape(Mx, 3 * D, D).tn) == 0;
-          EpiQKVFrag epi{big, kv, map, D, win.Pw, qscale2, swap ? 2 * D : 1 << 30};
+        if (p.attn_mfma) {  // spatial: sequence (b, f) = rows (b*Fw + f)*Pw + i; the projection writes V transposed
+          bf16* vt = reinterpret_cast<bf16*>(big) + 3 * M * D;  // behind the q / k / v rows
+          EpiStoreQKVt epi{big, (int64_t)3 * D, vt, D, win.Pw, qscale2};
           SI_TRY((launch_gemm_sel<T, false>("qkv", ring, a, (int64_t)D, wqkv, M, Mx, 3 * D, D, epi, st)));
-          SI_TRY(launch_attention_mfma("self_attn", big, kv, a, (int64_t)D, S, win.Pw, win.Pw, p.heads, p.d, 1, st, self_frag ? D : 0));
+          SI_TRY(launch_attention_mfma("self_attn", big, (int64_t)3 * D, big + D, (int64_t)3 * D, vt, a, (int64_t)D, p.B * win.Fw,
+                                       win.Pw, win.Pw, win.Pw, p.heads, 1, st, self_frag ? D : 0));
           self_done = true;
         }
       }
@@ -946,14 +956,20 @@ static si_status run_block(const Plan& p, const si_tensor5* x, const si_block_we
       }
       if (spatial && !p.post_fused) {
         SI_TRY(launch_layer_norm<T>("ln2", h, a, M, D, w->ln2_g, w->ln2_b, w->ln_eps, nullptr, win.Pw, win.Fw, win.f0, st, ring));
-        if constexpr (sizeof(T) == 2) {  // keys / values: the context rows of the batch entry, shared by its frames
-          EpiQFrag epi{big, AttnFragMap{p.heads, p.d, (win.Pw + 31) / 32}, win.Pw, qscale2};
+        {
+          EpiStore<T> epi{big, (int64_t)D, nullptr, p.attn_mfma ? qscale2 : 1.f};
           SI_TRY((launch_gemm_sel<T, false>("q2", ring, a, (int64_t)D, wq2, M, Mx, D, D, epi, st)));
-          SI_TRY(launch_attention_mfma("cross_attn", big, reinterpret_cast<const bf16*>(ws + p.off_ctxfrag), a, (int64_t)D, p.B * win.Fw,
-                                       win.Pw, p.Mc, p.heads, p.d, win.Fw, st, cross_frag ? D : 0));
-        } else {
-          EpiStore<T> epi{big, (int64_t)D, nullptr};
-          SI_TRY((launch_gemm_sel<T, false>("q2", ring, a, (int64_t)D, wq2, M, Mx, D, D, epi, st)));
+        }
+        bool cross_done = false;
+        if constexpr (sizeof(T) == 2) {
+          if (p.attn_mfma) {  // keys / values: the context rows of the batch entry, shared by its frames
+            SI_TRY(launch_attention_mfma("cross_attn", big, (int64_t)D, ctxkv, (int64_t)2 * D,
+                                         reinterpret_cast<const bf16*>(ws + p.off_ctxvt), a, (int64_t)D, p.B * win.Fw, win.Pw,
+                                         p.Mc, p.Mcp, p.heads, win.Fw, st, cross_frag ? D : 0));
+            cross_done = true;
+          }
+        }
+        if (!cross_done) {
           AttnArgs at;
           at.q = big; at.k = ctxkv; at.v = ctxkv + D; at.o = a;
           at.ldq = D; at.ldk = at.ldv = (int64_t)2 * D; at.ldo = D;
@@ -961,7 +977,7 @@ static si_status run_block(const Plan& p, const si_tensor5* x, const si_block_we
           at.S = p.B * win.Fw; at.Nq = win.Pw; at.Nk = p.Mc;
           at.qmap = SeqMap{1, (int64_t)win.Pw, 0, 1};
           at.kmap = SeqMap{win.Fw, (int64_t)p.Mc, 0, 1};
-          SI_TRY(launch_attention<T>("cross_attn", at, st));
+          SI_TRY(launch_attention<T>("cross_attn", at, st, cross_frag ? D : 0));
         }
         if (!fused_ffn) {
           EpiResidual<T> epi{h, (int64_t)D, cT(w->bo2), 1, nullptr};
