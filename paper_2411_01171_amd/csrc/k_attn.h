@@ -118,117 +118,171 @@ __global__ __launch_bounds__(256) void attn_valu_kernel(AttnArgs a) {
   }
 }
 
-// Short sequences in 16-bit storage (temporal blocks on the staged path: at most 32 tokens per
-// sequence, any head dimension d = 8 .. 128, d % 8 == 0) on the matrix cores: one wavefront per
-// (sequence, head), no LDS.  A lane's 16-byte pieces of the q, k and v rows are MFMA operands as they
-// stand (lane (token r, half g): channels 16 ks + 8 g + e), so S^T[key, query] = K Q^T takes both
-// straight from memory, and the softmax result registers are the column operand of O^T += V^T P^T.
-// V^T comes from V by a product with the identity (V as row operand, 16-channel slices of I as column
-// operand: exact, and the result registers are keys in the order P^T has them).  P enters as the sum of
-// two bf16 values (p and what its rounding leaves), so the probabilities keep 16 significand bits.
-// Bound by the gather of q/k/v rows, which lie Pw rows apart: a workgroup takes one head of 4 consecutive
-// sequences (adjacent token rows on either side), the heads of those sequences follow each other, and
-// every XCD gets a contiguous share of that list, so that an L2 sees whole lines.
-// 500 sequences of 14 frames, 8 heads of 80: 54.7 us (vector-ALU online softmax) -> 13.4; 128 of 16
-// frames, 20 heads of 64: 21.3 us (one lane per query, fp32 dot products) -> 12.7, and the out-projection
-// behind it reads fragments instead of rows (24.1 -> 20.7 us).
-// o_frag: o is a fragment-order buffer of that many channels per token instead of rows.
-template <int KS, int DB>
-__global__ __launch_bounds__(256, KS <= 5 ? 4 : 2) void attn_short_kernel(AttnArgs a, int o_frag) {
+// Short sequences in 16-bit storage (at most 32 tokens per sequence: temporal blocks on the staged path, small maps),
+// head dimension d = 8 D8, on the fp32 matrix instructions: one wavefront per (sequence, head), no LDS.  Scores,
+// probabilities and sums are fp32 with exact expf; v_mfma_f32_16x16x4_f32 is a chain of fused multiply-adds in k order,
+// so the results are those of the vector ALUs that worked channel by channel and key by key.
+// FT: 16-token tiles.  Operands as in attn_f32mma_kernel: S^T = K Q^T with key 4 j + g of a tile in register j of lane
+// group g, whose probabilities are then the column operand of O^T += V^T P^T.  A lane loads 16-byte pieces of its q and
+// k rows (group g of every four); two lane-half exchanges hand it the channels 4 s + g that the products want.
+// Row sums: heads of 64 add even and odd keys in sequence, the halves last; others add by halving, as a reduction over
+// 64 lanes does.  Both orders are what results of these calls have always had.
+// Bound by the gather of q/k/v rows, which lie Pw rows apart: a workgroup takes one head of 4 consecutive sequences
+// (adjacent token rows on either side), the heads of those sequences follow each other, and every XCD gets a
+// contiguous share of that list, so that an L2 sees whole lines.  500 sequences of 14 frames, 8 heads of 80: 54.7 us
+// (attn_valu_kernel) -> 12.6; 128 of 16 frames, 20 heads of 64: 21.3 us (one lane per query) -> 10.5.
+// o_frag: 0, or o is a fragment-order buffer of that many channels per token.
+template <int D8, int FT>
+__global__ __launch_bounds__(256) void attn_short_kernel(AttnArgs a, int o_frag) {
+  constexpr int NS = 2 * D8, NB = (D8 + 3) / 4, DB = (D8 + 1) / 2;  // steps of 4 channels, 32-channel loads, 16-channel blocks
   const int lane = threadIdx.x % kWave;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  const int r = lane % 32, g = lane / 32;
-  const int groups = (a.S + 3) / 4, ntiles = groups * a.heads, chunk = (ntiles + 7) / 8;
-  const int work = (int)(blockIdx.x % 8) * chunk + (int)(blockIdx.x / 8);
-  if (work >= ntiles || (int)(blockIdx.x / 8) >= chunk) return;
-  const int s = (work / a.heads) * 4 + wave, hc = (work % a.heads) * a.d;
-  if (s >= a.S) return;  // whole wavefront leaves; no block-wide barrier below
-  const int F = a.Nk;
-  const int rr = r < F ? r : F - 1;  // rows past the sequence repeat the last one: masked as keys, not stored as queries
-  const unsigned short* qrow = static_cast<const unsigned short*>(a.q) + a.qmap.row(s, rr) * a.ldq + hc + 8 * g;
-  const unsigned short* krow = static_cast<const unsigned short*>(a.k) + a.kmap.row(s, rr) * a.ldk + hc + 8 * g;
-  const unsigned short* vrow = static_cast<const unsigned short*>(a.v) + a.kmap.row(s, rr) * a.ldv + hc + 8 * g;
-  u32x4_t qf[KS], kf[KS], vf[KS];
-#pragma unroll
-  for (int ks = 0; ks < KS; ++ks) {
-    const bool in = 16 * ks + 8 * g < a.d;  // only the last k-step of an odd number of 8-channel pieces is half empty
-    qf[ks] = kf[ks] = vf[ks] = u32x4_t{0, 0, 0, 0};
-    if (in) {
-      qf[ks] = *reinterpret_cast<const u32x4_t*>(qrow + 16 * ks);
-      kf[ks] = *reinterpret_cast<const u32x4_t*>(krow + 16 * ks);
-      vf[ks] = *reinterpret_cast<const u32x4_t*>(vrow + 16 * ks);
-    }
-  }
-  auto mfma = [](u32x4_t row, u32x4_t col, f32x16_t acc) {
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, row), __builtin_bit_cast(bf16x8_t, col), acc, 0, 0, 0);
-  };
-  f32x16_t zero;
-#pragma unroll
-  for (int e = 0; e < 16; ++e) zero[e] = 0.f;
-  f32x16_t sc = zero;
-#pragma unroll
-  for (int ks = 0; ks < KS; ++ks) sc = mfma(kf[ks], qf[ks], sc);
-
-  // softmax over the keys: this lane holds keys 8 (e / 4) + 4 g + e % 4 of query r, lane ^ 32 the others
-  const float scale2 = a.scale * 1.4426950408889634f;
-  float m = -INFINITY;
-#pragma unroll
-  for (int e = 0; e < 16; ++e) {
-    sc[e] = 8 * (e / 4) + 4 * g + (e % 4) < F ? sc[e] * scale2 : -INFINITY;
-    m = fmaxf(m, sc[e]);
-  }
-  m = fmaxf(m, __shfl_xor(m, 32, kWave));
-  unsigned hi[8], lo[8];
-  float l = 0.f;
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const float p0 = __builtin_amdgcn_exp2f(sc[2 * i] - m), p1 = __builtin_amdgcn_exp2f(sc[2 * i + 1] - m);
-    l += p0 + p1;
-    hi[i] = (unsigned)float_to_bf16_bits(p0) | ((unsigned)float_to_bf16_bits(p1) << 16);
-    lo[i] = (unsigned)float_to_bf16_bits(p0 - __uint_as_float(hi[i] << 16)) |
-            ((unsigned)float_to_bf16_bits(p1 - __uint_as_float(hi[i] & 0xffff0000u)) << 16);
-  }
-  l += __shfl_xor(l, 32, kWave);
-  const float inv = 1.f / l;
-
-  // slices of the identity: k-step s2 of a 32-channel block, lane (column r, half g): element e is 1 where 16 s2 + 8 g + e == r
-  u32x4_t eye[2];
-#pragma unroll
-  for (int s2 = 0; s2 < 2; ++s2)
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      const int at = r - (16 * s2 + 8 * g + 2 * w);
-      eye[s2][w] = at == 0 ? 0x3f80u : at == 1 ? 0x3f800000u : 0u;
-    }
-  const int64_t orow = a.qmap.row(s, rr);
+  const int r = lane % 16, g = lane / 16;
+  const unsigned short* Q = static_cast<const unsigned short*>(a.q);
+  const unsigned short* Kp = static_cast<const unsigned short*>(a.k);
+  const unsigned short* Vp = static_cast<const unsigned short*>(a.v);
   unsigned short* O = static_cast<unsigned short*>(a.o);
+  const int F = a.Nk;
+  const int64_t ntiles = (int64_t)((a.S + 3) / 4) * a.heads, chunk = (ntiles + 7) / 8;
+  for (int64_t it = blockIdx.x / 8; it < chunk; it += gridDim.x / 8) {
+    const int64_t work = (int64_t)(blockIdx.x % 8) * chunk + it;
+    if (work >= ntiles) return;
+    const int s = (int)(work / a.heads) * 4 + wave, hc = (int)(work % a.heads) * a.d;
+    if (s >= a.S) continue;  // no barrier below
+
+    // rows past the sequence repeat its last one, pieces past the head its last one: their scores are overwritten,
+    // their values cleared, their columns and channels not stored
+    u32x4_t qr[FT][NB], kr[FT][NB];
+    float vf[FT][4][DB];
 #pragma unroll
-  for (int b = 0; b < DB; ++b) {
-    f32x16_t vt = mfma(vf[2 * b], eye[0], zero);
-    if (2 * b + 1 < KS) vt = mfma(vf[2 * b + 1 < KS ? 2 * b + 1 : 0], eye[1], vt);
-    f32x16_t o = zero;
+    for (int t = 0; t < FT; ++t) {
+      const int qi = 16 * t + r, ki = 16 * t + 4 * (r % 4) + r / 4;
+      const unsigned short* qrow = Q + a.qmap.row(s, qi < F ? qi : F - 1) * a.ldq + hc;
+      const unsigned short* krow = Kp + a.kmap.row(s, ki < F ? ki : F - 1) * a.ldk + hc;
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      u32x4_t vrow4;
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        vrow4[i] = (unsigned)float_to_bf16_bits(vt[8 * t + 2 * i]) | ((unsigned)float_to_bf16_bits(vt[8 * t + 2 * i + 1]) << 16);
-      o = mfma(vrow4, u32x4_t{hi[4 * t], hi[4 * t + 1], hi[4 * t + 2], hi[4 * t + 3]}, o);
-      o = mfma(vrow4, u32x4_t{lo[4 * t], lo[4 * t + 1], lo[4 * t + 2], lo[4 * t + 3]}, o);
+      for (int n = 0; n < NB; ++n) {
+        const int c8 = 4 * n + g < D8 ? 4 * n + g : D8 - 1;
+        qr[t][n] = *reinterpret_cast<const u32x4_t*>(qrow + 8 * c8);
+        kr[t][n] = *reinterpret_cast<const u32x4_t*>(krow + 8 * c8);
+      }
     }
-    // registers 8 hf .. + 7: channels 32b + 16hf + {4g .. +3, 8 + 4g .. +3}; one lane^32 exchange per register
-    // pair hands each lane the 8 consecutive channels 32b + 16hf + 8g .. +7
 #pragma unroll
-    for (int hf = 0; hf < 2; ++hf) {
-      unsigned w[4];
+    for (int t = 0; t < FT; ++t)
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-        w[i] = (unsigned)float_to_bf16_bits(o[8 * hf + 2 * i] * inv) | ((unsigned)float_to_bf16_bits(o[8 * hf + 2 * i + 1] * inv) << 16);
-      const auto x = __builtin_amdgcn_permlane32_swap(w[0], w[2], false, false);
-      const auto y = __builtin_amdgcn_permlane32_swap(w[1], w[3], false, false);
-      const int c = 32 * b + 16 * hf + 8 * g;
-      if (r < F && c < a.d)
-        *reinterpret_cast<u32x4_t*>(O + (o_frag ? act_offset(orow, hc + c, o_frag) : orow * a.ldo + hc + c)) = u32x4_t{x[0], y[0], x[1], y[1]};
+      for (int j = 0; j < 4; ++j) {
+        const int vi = 16 * t + 4 * j + g;
+        const unsigned short* vrow = Vp + a.kmap.row(s, vi < F ? vi : F - 1) * a.ldv + hc;
+#pragma unroll
+        for (int b = 0; b < DB; ++b) {
+          const float v = bf16_bits_to_float(vrow[16 * b + r < 8 * D8 ? 16 * b + r : r % 8]);
+          vf[t][j][b] = vi < F ? v : 0.f;
+        }
+      }
+    // step st of a row whose pieces 4 n + g the lane groups hold: channel 4 st + g
+    auto steps = [&](const u32x4_t(&raw)[NB], float(&out)[NS]) {
+#pragma unroll
+      for (int n = 0; n < NB; ++n) {
+        unsigned v[8];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          v[2 * e] = raw[n][e] << 16;
+          v[2 * e + 1] = raw[n][e] & 0xffff0000u;
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {  // channels 4 h .. + 3 of the piece: group bits and channel bits change places
+          const auto x0 = __builtin_amdgcn_permlane32_swap(v[4 * h], v[4 * h + 2], false, false);
+          const auto x1 = __builtin_amdgcn_permlane32_swap(v[4 * h + 1], v[4 * h + 3], false, false);
+          const auto y0 = __builtin_amdgcn_permlane16_swap(x0[0], x1[0], false, false);  // pieces 0, 1
+          const auto y1 = __builtin_amdgcn_permlane16_swap(x0[1], x1[1], false, false);  // pieces 2, 3
+          const unsigned p[4] = {y0[0], y0[1], y1[0], y1[1]};
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (8 * n + 2 * i + h < NS) out[8 * n + 2 * i + h] = __uint_as_float(p[i]);
+        }
+      }
+    };
+    const f32x4_t zero = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    f32x4_t sc[FT][FT];  // [query tile][key tile]
+    {
+      float kf[FT][NS];
+#pragma unroll
+      for (int t = 0; t < FT; ++t) steps(kr[t], kf[t]);
+#pragma unroll
+      for (int u = 0; u < FT; ++u) {
+        float qf[NS];
+        steps(qr[u], qf);
+#pragma unroll
+        for (int t = 0; t < FT; ++t) sc[u][t] = zero;
+#pragma unroll
+        for (int i = 0; i < NS; ++i)
+#pragma unroll
+          for (int t = 0; t < FT; ++t) sc[u][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[t][i], qf[i] * a.scale, sc[u][t], 0, 0, 0);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < FT; ++u) {
+      float m = -INFINITY;
+#pragma unroll
+      for (int t = 0; t < FT; ++t)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          if (16 * t + 4 * j + g >= F) sc[u][t][j] = -INFINITY;
+          m = fmaxf(m, sc[u][t][j]);
+        }
+      m = fmaxf(m, __shfl_xor(m, 32, kWave));
+      m = fmaxf(m, __shfl_xor(m, 16, kWave));
+#pragma unroll
+      for (int t = 0; t < FT; ++t)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) sc[u][t][j] = expf(sc[u][t][j] - m);  // a key beyond the sequence: exp(-inf) = 0
+      float l;
+      if constexpr (D8 == 8) {  // even keys are in groups 0 and 2, odd ones in 1 and 3
+        l = 0.f;
+#pragma unroll
+        for (int t = 0; t < FT; ++t)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const float own = sc[u][t][j], other = __shfl_xor(own, 32, kWave);
+            l += g & 2 ? other : own;
+            l += g & 2 ? own : other;
+          }
+      } else {
+        float p[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) p[j] = FT == 2 ? sc[u][0][j] + sc[u][FT - 1][j] : sc[u][0][j];
+        l = (p[0] + p[2]) + (p[1] + p[3]);
+        l += __shfl_xor(l, 32, kWave);
+      }
+      l += __shfl_xor(l, 16, kWave);
+      const float inv = 1.f / l;
+      f32x4_t o[DB];
+#pragma unroll
+      for (int b = 0; b < DB; ++b) o[b] = zero;
+#pragma unroll
+      for (int t = 0; t < FT; ++t)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+          for (int b = 0; b < DB; ++b) o[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[t][j][b], sc[u][t][j], o[b], 0, 0, 0);
+      // register j of block b: channel 16 b + 4 g + j.  Of two blocks, one exchange between neighbouring groups leaves
+      // even groups with a whole 16-byte piece of the first, odd ones with one of the second
+      const int qi = 16 * u + r;
+      const int64_t row = a.qmap.row(s, qi < F ? qi : 0);
+      auto word = [&](int b, int i) {
+        return (unsigned)float_to_bf16_bits(o[b][2 * i] * inv) | ((unsigned)float_to_bf16_bits(o[b][2 * i + 1] * inv) << 16);
+      };
+      auto dst = [&](int c) { return O + (o_frag ? act_offset(row, hc + c, o_frag) : row * a.ldo + hc + c); };
+#pragma unroll
+      for (int b = 0; b + 1 < DB; b += 2) {
+        const auto x = __builtin_amdgcn_permlane16_swap(word(b, 0), word(b + 1, 0), false, false);
+        const auto y = __builtin_amdgcn_permlane16_swap(word(b, 1), word(b + 1, 1), false, false);
+        const int c = 16 * (b + g % 2) + 8 * (g / 2);
+        if (qi < F && c < 8 * D8) *reinterpret_cast<u32x4_t*>(dst(c)) = u32x4_t{x[0], y[0], x[1], y[1]};
+      }
+      if constexpr (DB % 2 == 1) {
+        const int c = 16 * (DB - 1) + 4 * g;
+        if (qi < F && c < 8 * D8) *reinterpret_cast<uint2*>(dst(c)) = make_uint2(word(DB - 1, 0), word(DB - 1, 1));
+      }
     }
   }
 }

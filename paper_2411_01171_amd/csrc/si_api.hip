@@ -444,21 +444,6 @@ static si_status launch_gemm_sel(const char* stage, bool as_ring, const T* A, in
   return launch_gemm<T, F16>(stage, A, lda, Wp, M, N, K, epi, st);
 }
 
-// Calls f(integral_constant<KS>, integral_constant<DB>) for head dimension d = 8 .. 128.
-template <class Fn>
-static void attn_dispatch(int d, Fn f) {
-  switch ((d + 15) / 16) {
-    case 1: f(std::integral_constant<int, 1>(), std::integral_constant<int, 1>()); break;
-    case 2: f(std::integral_constant<int, 2>(), std::integral_constant<int, 1>()); break;
-    case 3: f(std::integral_constant<int, 3>(), std::integral_constant<int, 2>()); break;
-    case 4: f(std::integral_constant<int, 4>(), std::integral_constant<int, 2>()); break;
-    case 5: f(std::integral_constant<int, 5>(), std::integral_constant<int, 3>()); break;
-    case 6: f(std::integral_constant<int, 6>(), std::integral_constant<int, 3>()); break;
-    case 7: f(std::integral_constant<int, 7>(), std::integral_constant<int, 4>()); break;
-    default: f(std::integral_constant<int, 8>(), std::integral_constant<int, 4>()); break;
-  }
-}
-
 // Calls f(integral_constant<d / 8>) for head dimension d = 8 .. 128, a multiple of 8.
 template <int D8 = 1, class Fn>
 static void head_dispatch(int d, Fn f) {
@@ -475,15 +460,17 @@ static si_status launch_attention(const char* stage, const AttnArgs& a, hipStrea
   if (a.S <= 0 || a.Nq <= 0) return SI_OK;
   StageScope scope(stage, st);
   if constexpr (sizeof(T) == 2) {
-    if (a.Nq == a.Nk && a.Nk <= 32) {  // sequences of up to 32 tokens: one wavefront per (sequence, head)
-      const int64_t wgs = (int64_t)((a.S + 3) / 4) * a.heads;
-      attn_dispatch(a.d, [&](auto ks, auto db) {
-        attn_short_kernel<ks.value, db.value><<<(unsigned)((wgs + 7) / 8 * 8), 256, 0, st>>>(a, o_frag);
+    const int64_t most = 1 << 20;  // a launch is less than 2^32 threads; the kernels walk longer lists
+    auto grid = [&](int64_t tiles) { return (unsigned)(((tiles < most ? tiles : most) + 7) / 8 * 8); };
+    if (a.Nq == a.Nk && a.Nk <= 32) {  // one wavefront per (sequence, head)
+      const unsigned wgs = grid((int64_t)((a.S + 3) / 4) * a.heads);
+      head_dispatch(a.d, [&](auto d8) {
+        if (a.Nk <= 16) attn_short_kernel<d8.value, 1><<<wgs, 256, 0, st>>>(a, o_frag);
+        else attn_short_kernel<d8.value, 2><<<wgs, 256, 0, st>>>(a, o_frag);
       });
     } else {
-      const int64_t tiles = (int64_t)((a.Nq + 127) / 128) * a.heads * a.S, most = 1 << 20;  // a launch is less than 2^32 threads
-      const unsigned grid = (unsigned)(((tiles < most ? tiles : most) + 7) / 8 * 8);
-      head_dispatch(a.d, [&](auto d8) { attn_f32mma_kernel<d8.value><<<grid, 256, 0, st>>>(a, o_frag); });
+      const unsigned wgs = grid((int64_t)((a.Nq + 127) / 128) * a.heads * a.S);
+      head_dispatch(a.d, [&](auto d8) { attn_f32mma_kernel<d8.value><<<wgs, 256, 0, st>>>(a, o_frag); });
     }
   } else {
     constexpr int QB = 4;

@@ -64,3 +64,73 @@ def test_spatial(heads, d, hw, cross):
     e = errors(run_block(spec, x, w, ctx, 1), ref, x)
     print(e)
     assert e["rel_l2_branch"] <= BRANCH_REL
+
+
+# temporal sequences: q, k and v themselves are read off the device (one-frame sequences return their values), so that
+# the comparison holds attention alone
+VALUE_GAIN = 4096.0  # keeps the output in the normal range of the fp16 operand of proj_out
+
+
+def _temporal_inputs(F, heads, d, hw):
+    """Frames 2 i and 2 i + 1 agree in the channels that scores come from and are opposite in those that values come
+    from; a weak share of the latter makes their scores differ by about 1e-5."""
+    D = C = heads * d
+    spec = tiny_spec(wl.TEMPORAL, B=1, C=C, F=F, H=hw[0], W=hw[1], heads=heads, dim_head=d, groups=C // 8, dtype="bf16")
+    rng = np.random.default_rng(F + d)
+    P, half, quarter = hw[0] * hw[1], D // 2, D // 4
+    x = np.zeros((1, C, F, P))
+    x[0, :SCORE_CH] = np.repeat(rng.standard_normal((SCORE_CH, (F + 1) // 2, P)), 2, axis=1)[:, :F]
+    x[0, SCORE_CH:quarter] = np.repeat(rng.standard_normal((quarter - SCORE_CH, (F + 1) // 2, P)), 2, axis=1)[:, :F]
+    x[0, SCORE_CH:quarter, 1::2] *= -1
+    if F % 2:
+        x[0, SCORE_CH:quarter, F - 1] = 0  # the odd frame out has no values
+    w = {k: np.zeros_like(v) if not k.endswith("_g") else v for k, v in wl.make_weights(spec).items()}
+    for c in range(quarter):  # every channel and its negative: LayerNorm's mean is zero, its output opposite where x is
+        w["w_in"][c, c] = 1
+        w["w_in"][c, quarter + c] = -1
+    for h in range(heads):
+        for c in range(SCORE_CH // 2):
+            w["wq"][c, h * d + c] = 0.25
+            w["wk"][c, h * d + c] = 1
+            w["wq"][c, h * d + 4 + c] = 2.0 ** -8
+            w["wk"][SCORE_CH + c, h * d + 4 + c] = 2.0 ** -6
+    w["wv"][SCORE_CH:quarter] = rng.standard_normal((quarter - SCORE_CH, D)) / np.sqrt(quarter)
+    w["wo"][:half, half:] = VALUE_GAIN * np.eye(half)
+    w["w_out"][half:, half:] = np.eye(half)
+    return spec, wl.round_to_storage(x.reshape(1, C, F, *hw), "bf16"), {n: wl.round_to_storage(a, "bf16") for n, a in w.items()}
+
+
+def _attention_output(spec, x, w):
+    """The first half of the heads' channels of the attention output, [B, F, P, D / 2]."""
+    from gpu_helpers import run_block
+    half = spec.C // 2
+    out = run_block(spec, x, w, None, x.shape[3] * x.shape[4])[:, half:]
+    return (out / VALUE_GAIN).reshape(x.shape[0], half, x.shape[2], -1).transpose(0, 2, 3, 1)
+
+
+# the output's rounding to bf16 is 1.7e-3; expf and the sums add 6e-8 to each of the terms that differ by 1e-5.  Probabilities
+# of 16 significand bits move in steps of 4e-6: 2.5e-2 and more
+TEMPORAL_REL = 5e-3
+
+
+@pytest.mark.parametrize("F", [5, 14, 16, 31, 32])
+@pytest.mark.parametrize("heads,d", [(2, 40), (2, 64), (2, 80), (1, 128)])
+def test_temporal(heads, d, F):
+    spec, x, w = _temporal_inputs(F, heads, d, (3, 5))
+    D, half = heads * d, heads * d // 2
+    # every frame as a batch entry of one frame: attention hands back its value projection
+    single = wl.scaled(spec, B=F, F=1)
+    frames = np.ascontiguousarray(x.transpose(2, 1, 0, 3, 4))
+    q, k, v = (_attention_output(single, frames, dict(w, wv=w[n]))[:, 0].transpose(1, 0, 2) for n in ("wq", "wk", "wv"))
+    got = _attention_output(spec, x, w)[0].transpose(1, 0, 2)
+    nh = half // d  # whole heads among the channels that are read; a single head of 128 shows the first half of its own
+    for h in range(max(nh, 1)):
+        cs = slice(h * d, min(h * d + d, half))
+        ref = oracle.attention_ref(q[:, :, cs], k[:, :, cs], v[:, :, cs], 1) if nh else None
+        if ref is None:  # channels past the first eight hold no scores
+            s = np.einsum("pic,pjc->pij", q[..., :8], k[..., :8]) / np.sqrt(d)
+            p = np.exp(s - s.max(-1, keepdims=True))
+            ref = np.einsum("pij,pjc->pic", p / p.sum(-1, keepdims=True), v[:, :, cs])
+        e = np.linalg.norm(got[:, :, cs] - ref) / np.linalg.norm(ref)
+        print(F, heads, d, h, "rel", e, "size", np.sqrt(np.mean(ref ** 2)) / np.sqrt(np.mean(v[:, :, cs] ** 2)))
+        assert e <= TEMPORAL_REL
