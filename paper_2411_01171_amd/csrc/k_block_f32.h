@@ -9,6 +9,10 @@
 // conflict-free LDS read of 64 consecutive floats.  The next 64 k-values of weight are loaded before the MFMAs
 // of the current ones, the first ones of the next contraction before the barriers in between.
 //
+// The results are those of the staged fp32 kernels bit for bit, so that a call's windows may take either: the matrix
+// instruction is a chain of fused multiply-adds in k order, as gemm_f32_kernel's and attn_valu_kernel's loops are, and
+// the sums of LayerNorm and softmax are added in layer_norm_kernel's and attn_valu_kernel's order.
+//
 // Whole calls, start (one launch per operator and window, 49 in the first row) -> this kernel:
 //   D 64, 8 frames of 8x8, B 1                  455 -> 26 us
 //   D 64, 16 frames of 20x20, B 2, 4 windows    492 -> 71 us
@@ -146,30 +150,42 @@ __global__ __launch_bounds__(NT) void temporal_block_f32_kernel(BlockF32Args a) 
   const std::integral_constant<int, 2> two;
   auto bias = [](const float* p, int n) { return p ? p[n] : 0.f; };
 
-  // LayerNorm of the residual columns into `as`
+  // LayerNorm of the residual columns into `as`.  Sums in layer_norm_kernel's order: 64 partial sums, number L over the
+  // rows 4 L .. + 3 of every 256, added by halves.  A thread forms RL of them (the top bits of L); the lanes of a wavefront
+  // hold the next bits, the wavefronts the lowest.
   auto layer_norm = [&](const float* g, const float* bt, const float* pe) {
-    constexpr int NP = NT / TK;
-    const int t = tid % TK, part = tid / TK;
-    auto total = [&](float v) {
+    constexpr int NP = NT / TK, RL = kWave / NP, PW = kWave / TK;
+    const int t = tid % TK, part = tid / TK, pin = lane / TK;
+    auto total = [&](auto quad) {
+      float v[RL];
 #pragma unroll
-      for (int o = TK; o < kWave; o <<= 1) v += __shfl_xor(v, o, kWave);
+      for (int k = 0; k < RL; ++k) {
+        v[k] = 0.f;
+        for (int n = 4 * ((k * PW + pin) * NWV + wave); n < D; n += 4 * kWave) v[k] += quad(hs + n * TK + t);
+      }
+#pragma unroll
+      for (int h = RL / 2; h > 0; h >>= 1)
+#pragma unroll
+        for (int k = 0; k < h; ++k) v[k] += v[k + h];
+#pragma unroll
+      for (int o = kWave / 2; o >= TK; o >>= 1) v[0] += __shfl_xor(v[0], o, kWave);
       __syncthreads();  // the previous use of red
-      if (lane < TK) red[wave * TK + lane] = v;
+      if (lane < TK) red[wave * TK + lane] = v[0];
       __syncthreads();
-      float s = 0.f;
+      float s[NWV];
 #pragma unroll
-      for (int w = 0; w < NWV; ++w) s += red[w * TK + t];
-      return s;
+      for (int w = 0; w < NWV; ++w) s[w] = red[w * TK + t];
+#pragma unroll
+      for (int h = NWV / 2; h > 0; h >>= 1)
+#pragma unroll
+        for (int w = 0; w < h; ++w) s[w] += s[w + h];
+      return s[0];
     };
-    float s = 0.f;
-    for (int n = part; n < D; n += NP) s += hs[n * TK + t];
-    const float mean = total(s) / (float)D;
-    float q = 0.f;
-    for (int n = part; n < D; n += NP) {
-      const float dv = hs[n * TK + t] - mean;
-      q = fmaf(dv, dv, q);
-    }
-    const float rstd = rsqrtf(total(q) / (float)D + a.ln_eps);
+    const float mean = total([&](const float* x) { return (x[0] + x[TK]) + (x[2 * TK] + x[3 * TK]); }) / (float)D;
+    const float rstd = rsqrtf(total([&](const float* x) {
+                                const float dx = x[0] - mean, dy = x[TK] - mean, dz = x[2 * TK] - mean, dw = x[3 * TK] - mean;
+                                return (dx * dx + dy * dy) + (dz * dz + dw * dw);
+                              }) / (float)D + a.ln_eps);
     const float* perow = pe ? pe + (int64_t)(t % F) * D : nullptr;  // columns start at whole sequences
     for (int n = part; n < D; n += NP) {
       float y = (hs[n * TK + t] - mean) * rstd * (g ? g[n] : 1.f) + (bt ? bt[n] : 0.f);
@@ -226,14 +242,22 @@ __global__ __launch_bounds__(NT) void temporal_block_f32_kernel(BlockF32Args a) 
     const int t = e % TK, h = e / TK;
     if (t >= ntok) continue;
     float* row = sc + h * F * TK + t;
-    float m = -INFINITY, l = 0.f;
-    for (int j = 0; j < F; ++j) m = fmaxf(m, row[j * TK]);
-    for (int j = 0; j < F; ++j) {
-      const float w = expf(row[j * TK] - m);
-      row[j * TK] = w;
-      l += w;
+    float m = -INFINITY, w[TK];  // F <= TK
+#pragma unroll
+    for (int j = 0; j < TK; ++j) {
+      w[j] = row[(j < F ? j : 0) * TK];
+      m = fmaxf(m, w[j]);
     }
-    sc[(a.heads * F + h) * TK + t] = 1.f / l;
+#pragma unroll
+    for (int j = 0; j < TK; ++j) {
+      if (j < F) row[j * TK] = w[j] = expf(w[j] - m);
+      else w[j] = 0.f;
+    }
+#pragma unroll
+    for (int o = TK / 2; o > 0; o >>= 1)  // the row sum by halves, as attn_valu_kernel's lanes add theirs
+#pragma unroll
+      for (int j = 0; j < o; ++j) w[j] += w[j + o];
+    sc[(a.heads * F + h) * TK + t] = 1.f / w[0];
   }
   __syncthreads();
   for (int e = tid; e < D * TK; e += NT) {
