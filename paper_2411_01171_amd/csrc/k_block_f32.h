@@ -50,7 +50,7 @@ static inline int64_t block_f32_rows(int C, int D, int heads, int F) {
 }
 
 template <int TT, int CAP, int NT>
-__global__ __launch_bounds__(NT) void temporal_block_f32_kernel(BlockF32Args a) {
+__global__ __launch_bounds__(NT, 4) void temporal_block_f32_kernel(BlockF32Args a) {
   constexpr int TK = 16 * TT, NWV = NT / kWave;
   __shared__ float lds[CAP];
   __shared__ float red[NWV * TK];
