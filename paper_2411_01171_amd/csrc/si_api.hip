@@ -223,15 +223,27 @@ static si_status make_plan(const si_tensor5* x, const si_block_weights* w, const
                   p->Mc <= 32 * kCrossTiles;
   // context values with keys contiguous (the post-attention kernel has its own form)
   p->off_ctxvt = take(p->attn_mfma && !p->post_fused ? (size_t)p->B * Dz * p->Mcp * es : 0);
-  // fp32 temporal blocks whose sequences and operands fit a workgroup's LDS take the one-kernel form.  The staged
-  // kernels remain better only where large windows of wide blocks leave many token columns empty (8000 tokens in one
-  // window, D = 320, 10 frames in 16 columns: 777 us against 945; in windows of 512 tokens 1732 against 230)
+  // fp32 temporal blocks whose sequences and operands fit a workgroup's LDS take the one-kernel form, except where a
+  // window is large enough to fill the staged kernels: the results are the same bits, so the window may decide.  The
+  // line is drawn in token columns, empty ones included, because those are what the one kernel pays for.  Measured on
+  // calls of one window (staged -> one kernel, us):
+  //   D  64: 10 frames, 25600 tokens  221 ->  151, 102400 tokens  531 ->  572; 16 frames, 102400 tokens  522 -> 381
+  //   D 128: 10 frames, 25600 tokens  430 ->  410, 102400 tokens 1381 -> 1592; 16 frames, 102400 tokens 1353 -> 1046
+  //   D 192: 12 frames,  9600 tokens  442 ->  380,  25600 tokens  754 ->  856; 16 frames, 102400 tokens 2660 -> 2404
+  //   D 256: 12 frames,  6400 tokens  521 ->  479,  12800 tokens  687 ->  795; 16 frames,  25600 tokens 1128 -> 1124
+  //   D 320: 12 frames,  4100 tokens  588 ->  482,   6400 tokens  670 ->  726; 16 frames,   9600 tokens  810 -> 732,
+  //          12800 tokens 896 -> 972, 102400 tokens 6670 -> 6040
+  //   D 384: 12 frames,  4100 tokens  752 ->  676,   6400 tokens  866 -> 1012; 16 frames,   6400 tokens  816 -> 685,
+  //          12800 tokens 1212 -> 1365
   p->f32_cols = 0;
   if (p->dtype == SI_F32 && p->kind == SI_BLOCK_TEMPORAL && p->F <= 32 && p->C % 16 == 0 && D % 16 == 0) {
-    const int cols = p->F <= 16 ? 16 : 32;
-    const bool filled = cols / p->F * p->F * 4 >= cols * 3;
-    if (block_f32_rows(p->C, p->D, p->heads, p->F) * cols <= kF32LdsFloats && (D <= 128 || filled || p->Mmax <= 4096))
-      p->f32_cols = cols;
+    const int cols = p->F <= 16 ? 16 : 32, nseq = cols / p->F;
+    const bool filled = nseq * p->F * 16 >= cols * 15;
+    const int64_t window = (p->Mmax / p->F + nseq - 1) / nseq * cols;  // token columns of the largest window
+    const int64_t most = filled ? (D <= 256 ? INT64_MAX : D <= 320 ? 12288 : 8192)
+                                : D <= 64 ? 131072 : D <= 128 ? 40960 : D <= 192 ? 16384 : D <= 256 ? 12288 : 8192;
+    const bool many = filled && window >= 65536;  // a partial last round of workgroups does not count any more
+    if (block_f32_rows(p->C, p->D, p->heads, p->F) * cols <= kF32LdsFloats && (window <= most || many)) p->f32_cols = cols;
   }
   // Ring GEMMs: 16-bit storage, every contraction length a multiple of the 32-wide k-tile, operand
   // buffers addressable with 32-bit byte offsets.
