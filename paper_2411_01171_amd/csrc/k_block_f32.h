@@ -39,7 +39,7 @@ struct BlockF32Args {
   const float *gn_g, *gn_b, *w_in, *b_in, *ln1_g, *ln1_b, *wq, *wk, *wv, *wo, *bo, *ln3_g, *ln3_b, *w1, *b1, *w2, *b2, *w_out, *b_out;
   const float* pe;  // [F, D] or NULL
   int B, C, F, G, heads, d, D, nseq;  // sequences per workgroup
-  int64_t P, groups;                   // groups of nseq sequences over all B*P
+  int64_t P, groups, first;            // groups of nseq sequences of this launch, sequence that it starts at
   float ln_eps, scale;
 };
 
@@ -65,7 +65,7 @@ __global__ __launch_bounds__(NT, 4) void temporal_block_f32_kernel(BlockF32Args 
   float* const bs = as + (C > D ? C : D) * TK;
 
   // token column t = (sequence i) * F + f
-  const int64_t s0 = grp * a.nseq, S = (int64_t)a.B * a.P;
+  const int64_t s0 = a.first + grp * a.nseq, S = (int64_t)a.B * a.P;
   const int nseq = (int)(s0 + a.nseq <= S ? a.nseq : S - s0), ntok = nseq * F;
   auto locate = [&](int t, int& b, int& f, int64_t& p) {
     const int i = t / F;

@@ -691,7 +691,9 @@ static si_status launch_gn_stats(const Plan& p, const T* X, const T* key, float 
   return SI_OK;
 }
 
-// The fp32 temporal block as one kernel: a launch covers every window (no intermediates outside LDS).
+// The fp32 temporal block as one kernel: a launch covers every window (no intermediates outside LDS).  A launch is less
+// than 2^32 threads, so 2^21 workgroups of up to 1024 at most; more sequences take several.
+constexpr int64_t kF32LaunchGroups = 1 << 21;
 static si_status run_block_f32(const Plan& p, const float* X, const si_block_weights* w, float* OUT, const float* stats,
                                const float* pe, hipStream_t st) {
   StageScope scope("temporal_block_f32", st);
@@ -704,18 +706,23 @@ static si_status run_block_f32(const Plan& p, const float* X, const si_block_wei
   a.pe = pe;
   a.B = p.B; a.C = p.C; a.F = p.F; a.G = p.G; a.heads = p.heads; a.d = p.d; a.D = p.D; a.P = p.P;
   a.nseq = p.f32_cols / p.F;
-  a.groups = ((int64_t)p.B * p.P + a.nseq - 1) / a.nseq;
   a.ln_eps = w->ln_eps; a.scale = 1.0f / sqrtf((float)p.d);
-  const unsigned grid = (unsigned)((a.groups + 7) / 8 * 8);
+  unsigned grid = 0;
   auto launch = [&](auto tt) {
     if (block_f32_rows(p.C, p.D, p.heads, p.F) * p.f32_cols <= kF32SmallFloats)
       temporal_block_f32_kernel<tt.value, kF32SmallFloats, kF32SmallThreads><<<grid, kF32SmallThreads, 0, st>>>(a);
     else
       temporal_block_f32_kernel<tt.value, kF32LdsFloats, kF32Threads><<<grid, kF32Threads, 0, st>>>(a);
   };
-  if (p.f32_cols == 16) launch(std::integral_constant<int, 1>());
-  else launch(std::integral_constant<int, 2>());
-  SI_CHECK_LAUNCH();
+  const int64_t groups = ((int64_t)p.B * p.P + a.nseq - 1) / a.nseq;
+  for (int64_t g0 = 0; g0 < groups; g0 += kF32LaunchGroups) {
+    a.first = g0 * a.nseq;
+    a.groups = groups - g0 < kF32LaunchGroups ? groups - g0 : kF32LaunchGroups;
+    grid = (unsigned)((a.groups + 7) / 8 * 8);
+    if (p.f32_cols == 16) launch(std::integral_constant<int, 1>());
+    else launch(std::integral_constant<int, 2>());
+    SI_CHECK_LAUNCH();
+  }
   return SI_OK;
 }
 

@@ -41,3 +41,29 @@ def test_window_length_does_not_change_the_bits(heads, d, F):
     e = errors(full, oracle.block_forward_ref(x, w, spec), x)
     print(e)
     assert e["rel_l2_branch"] <= BRANCH_REL
+
+
+def test_more_sequences_than_one_launch_holds():
+    """9 frames leave room for one sequence per workgroup: 2^23 + 4096 positions are 2^32 threads and more, five launches.  The map is a
+    1024-position one repeated, whose GroupNorm statistics it shares up to their fp32 rounding."""
+    import torch
+    import paper_2411_01171_amd as si
+    from gpu_helpers import AXIS, device_weights, to_dev
+    spec = tiny_spec(wl.TEMPORAL, B=1, C=16, F=9, H=1, W=1024, heads=2, dim_head=8, groups=8, dtype="f32")
+    small, w = wl.make_x(spec), wl.make_weights(spec, randomize_affine=True, matrix_std=0.05)
+    wd = device_weights(spec, w)
+
+    def run(x):
+        n = si.si_workspace_bytes(x, wd, None, AXIS[spec.slice_axis], 1024)
+        assert n > 0
+        out = torch.full_like(x, float("nan"))
+        si.si_block_forward(x, wd, None, out, AXIS[spec.slice_axis], 1024, torch.empty(n, dtype=torch.uint8, device="cuda"))
+        torch.cuda.synchronize()
+        return out
+
+    xs = to_dev(small, "f32")
+    reps = (1 << 23) // 1024 + 4
+    ref, got = run(xs), run(xs.repeat(1, 1, 1, 1, reps).view(1, 16, 9, reps, 1024).contiguous())
+    diff = (got - ref).abs().amax(dim=(0, 1, 2, 4))  # per repetition
+    # a mean or variance off by one fp32 rounding moves a normalised value by 1e-7 of its size, six contractions widen that
+    assert bool(torch.isfinite(diff).all()) and float(diff.max()) <= 1e-5 * float(ref.abs().max())
