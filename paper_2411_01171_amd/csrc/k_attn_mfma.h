@@ -45,23 +45,6 @@ constexpr int kAttnStages = 3;  // 48 KiB of LDS: three 4-wavefront workgroups p
 // key (within its 16-key group) whose score lands in MFMA row f of the group
 __host__ __device__ constexpr int kappa16(int f) { return f < 4 || f >= 12 ? f : (f < 8 ? f + 4 : f - 4); }
 
-// dst[(s*D + c)*Nkp + n] = src[(s*N + n)*ld + col0 + c]; zero for N <= n < Nkp.
-__global__ __launch_bounds__(256) void transpose_v_kernel(const bf16* __restrict__ src, int64_t ld, int col0, bf16* __restrict__ dst,
-                                                          int N, int Nkp, int D) {
-  __shared__ unsigned short tile[32][33];
-  const int tx = threadIdx.x % 32, ty = threadIdx.x / 32;  // 32 x 8
-  const int n0 = blockIdx.x * 32, c0 = blockIdx.y * 32, s = blockIdx.z;
-  for (int nn = ty; nn < 32; nn += 8) {
-    const int n = n0 + nn, c = c0 + tx;
-    tile[nn][tx] = (n < N && c < D) ? src[((int64_t)s * N + n) * ld + col0 + c].v : (unsigned short)0;
-  }
-  __syncthreads();
-  for (int cc = ty; cc < 32; cc += 8) {
-    const int n = n0 + tx, c = c0 + cc;
-    if (n < Nkp && c < D) dst[((int64_t)s * D + c) * Nkp + n].v = tile[tx][cc];
-  }
-}
-
 // Online softmax, per 32-key tile of this wavefront's 32 queries.  The queries arrive pre-scaled by
 // softmax scale * log2(e) (the projection's epilogue does it before its one rounding), so S^T is in
 // base-2 exponent units.  `minit` holds -m (the lane's reference maximum) in all 16 registers and is

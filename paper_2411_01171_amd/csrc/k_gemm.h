@@ -75,6 +75,30 @@ struct EpiStoreQKVt {
   }
 };
 
+// Key / value projection of the context for the matrix-core attention kernel: columns [0, D) (keys) row-major, the
+// value columns transposed, vt[(b*D + c)*Nkp + key] for context row m = b*Nk + key; keys Nk .. Nkp - 1 hold zeros.
+struct EpiStoreKVt {
+  static constexpr bool kRows8 = false;
+  bf16* k;
+  bf16* vt;
+  int D, Nk, Nkp;
+  __device__ __forceinline__ void operator()(int64_t m, int n0, const float (&v)[4]) const {
+    if (n0 < D) {
+      EpiStore<bf16>{k, (int64_t)D, nullptr}(m, n0, v);
+    } else {
+      const int64_t b = m / Nk;
+      const int key = (int)(m - b * Nk);
+      bf16* p = vt + (b * D + (n0 - D)) * Nkp + key;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        p[(int64_t)i * Nkp] = from_float<bf16>(v[i]);
+        if (key == Nk - 1)
+          for (int j = 1; key + j < Nkp; ++j) p[(int64_t)i * Nkp + j].v = 0;
+      }
+    }
+  }
+};
+
 // Residual stream (fp32): h[m, n] = (accumulate ? h[m, n] : 0) + acc + bias[n];
 // optionally the new value is also stored in copy (operand of proj_out): fp32 storage
 // as is; 16-bit storage as fp16 (11 significand bits, saturated at +-65504), row stride ld.

@@ -221,7 +221,7 @@ static si_status make_plan(const si_tensor5* x, const si_block_weights* w, const
   // channels (two 32-channel blocks), at most kCrossTiles key tiles
   p->post_fused = p->fused_nb == 10 && p->kind == SI_BLOCK_SPATIAL && p->attn_mfma && p->d == 64 && P % 128 == 0 &&
                   p->Mc <= 32 * kCrossTiles;
-  // context values with keys contiguous (the post-attention kernel has its own form)
+  // heads of 64: context values with keys contiguous (the post-attention kernel has its own form)
   p->off_ctxvt = take(p->attn_mfma && !p->post_fused ? (size_t)p->B * Dz * p->Mcp * es : 0);
   // fp32 temporal blocks whose sequences and operands fit a workgroup's LDS take the one-kernel form, except where a
   // window is large enough to fill the staged kernels: the results are the same bits, so the window may decide.  The
@@ -282,8 +282,9 @@ static si_status make_plan(const si_tensor5* x, const si_block_weights* w, const
   // when those are large enough.
   const size_t rehash_bytes = (size_t)p->B * p->F * p->G * 3 * sizeof(double) + 16;
   p->off_rehash = rehash_bytes <= p->lane_stride ? p->off_a : take(rehash_bytes);
-  // context keys / values; post_fused: re-ordered before the first window starts, likewise
-  const size_t ctx_bytes = (size_t)p->B * p->Mc * 2 * Dz * es;
+  // context keys / values (keys only where the values have a buffer of their own); post_fused: re-ordered before the
+  // first window starts, likewise
+  const size_t ctx_bytes = (size_t)p->B * p->Mc * (p->attn_mfma && !p->post_fused ? 1 : 2) * Dz * es;
   p->off_ctxkv = (p->post_fused && ctx_bytes <= p->lane_stride) ? p->off_a : take(ctx_bytes);
   const size_t act_end = off;
   // frame position table (a function of F and D only: written with the weight re-layout)
@@ -515,15 +516,6 @@ static si_status launch_attention_mfma(const char* stage, const bf16* q, int64_t
     a.ntiles = a.nqt * heads * S;
     attn_mfma_kernel<4><<<(unsigned)((a.ntiles + 7) / 8 * 8), 256, 0, st>>>(a);
   }
-  SI_CHECK_LAUNCH();
-  return SI_OK;
-}
-static si_status launch_transpose_v(const char* stage, const bf16* src, int64_t ld, int col0, bf16* dst, int S, int N, int Nkp,
-                                    int D, hipStream_t st) {
-  if (S <= 0 || N <= 0) return SI_OK;
-  StageScope scope(stage, st);
-  dim3 grid((unsigned)((Nkp + 31) / 32), (unsigned)((D + 31) / 32), (unsigned)S);
-  transpose_v_kernel<<<grid, 256, 0, st>>>(src, ld, col0, dst, N, Nkp, D);
   SI_CHECK_LAUNCH();
   return SI_OK;
 }
@@ -798,8 +790,18 @@ static si_status run_block(const Plan& p, const si_tensor5* x, const si_block_we
     if (p.f32_cols) return run_block_f32(p, X, w, OUT, stats, pe, st);
   }
   if (spatial) {
-    EpiStore<T> epi{ctxkv, (int64_t)2 * D, nullptr};
-    SI_TRY(launch_gemm<T>("ctx_kv", cT(ctx->ptr), (int64_t)p.Cc, wkv2, (int64_t)p.B * p.Mc, 2 * D, p.Cc, epi, st));
+    bool ctx_done = false;
+    if constexpr (sizeof(T) == 2) {
+      if (p.attn_mfma && !p.post_fused) {
+        EpiStoreKVt epi{ctxkv, reinterpret_cast<bf16*>(ws + p.off_ctxvt), D, p.Mc, p.Mcp};
+        SI_TRY(launch_gemm<T>("ctx_kv", cT(ctx->ptr), (int64_t)p.Cc, wkv2, (int64_t)p.B * p.Mc, 2 * D, p.Cc, epi, st));
+        ctx_done = true;
+      }
+    }
+    if (!ctx_done) {
+      EpiStore<T> epi{ctxkv, (int64_t)2 * D, nullptr};
+      SI_TRY(launch_gemm<T>("ctx_kv", cT(ctx->ptr), (int64_t)p.Cc, wkv2, (int64_t)p.B * p.Mc, 2 * D, p.Cc, epi, st));
+    }
     if constexpr (sizeof(T) == 2) {
       if (p.post_fused) {  // the context as fragments behind the post-attention kernel's weight stream
         StageScope scope("ctx_frags", st);
@@ -809,8 +811,7 @@ static si_status run_block(const Plan& p, const si_tensor5* x, const si_block_we
         pack_ctx_stream_kernel<10><<<wgs, 256, 0, st>>>(ctxkv, p.B, p.Mc, reinterpret_cast<u32x4_t*>(ws + p.off_ffn_stream), pitch,
                                                         n_main);
         SI_CHECK_LAUNCH();
-      } else if (p.attn_mfma)
-        SI_TRY(launch_transpose_v("ctx_vt", ctxkv, (int64_t)2 * D, D, reinterpret_cast<bf16*>(ws + p.off_ctxvt), p.B, p.Mc, p.Mcp, D, st));
+      }
     }
   }
 
@@ -969,7 +970,7 @@ static si_status run_block(const Plan& p, const si_tensor5* x, const si_block_we
         bool cross_done = false;
         if constexpr (sizeof(T) == 2) {
           if (p.attn_mfma) {  // keys / values: the context rows of the batch entry, shared by its frames
-            SI_TRY(launch_attention_mfma("cross_attn", big, (int64_t)D, ctxkv, (int64_t)2 * D,
+            SI_TRY(launch_attention_mfma("cross_attn", big, (int64_t)D, ctxkv, (int64_t)D,
                                          reinterpret_cast<const bf16*>(ws + p.off_ctxvt), a, (int64_t)D, p.B * win.Fw, win.Pw,
                                          p.Mc, p.Mcp, p.heads, win.Fw, st, cross_frag ? D : 0));
             cross_done = true;
