@@ -116,8 +116,9 @@ typedef struct {
  * intermediates of the slices in flight (Sec. 4.2.1: one sliced sub-feature at
  * a time; Sec. 4.2.2: up to si_windows_in_flight of them when slices are many
  * and small) plus slice-independent items (GroupNorm statistics, the
- * re-laid-out weights, the context keys/values).  `ctx` may be NULL for
- * temporal blocks.  Returns 0 if the arguments are invalid (the same checks
+ * re-laid-out weights, the context keys/values).  An fp32 temporal block that
+ * runs as one kernel over all windows re-lays out nothing and is counted with
+ * one window's intermediates.  `ctx` may be NULL for temporal blocks.  Returns 0 if the arguments are invalid (the same checks
  * as si_block_forward, pointers excepted).  Host-only; touches no GPU. */
 size_t si_workspace_bytes(const si_tensor5* x, const si_block_weights* w, const si_context* ctx,
                           int32_t axis, int64_t slice_len);

@@ -275,6 +275,9 @@ static si_status make_plan(const si_tensor5* x, const si_block_weights* w, const
   // on top in either case.
   const int64_t n_slices = (p->extent + p->slice_len - 1) / p->slice_len;
   p->lanes = (int)(n_slices / 4 < 1 ? 1 : n_slices / 4 > kMaxLanes ? kMaxLanes : n_slices / 4);
+  // One kernel for all windows: none has intermediates in memory.  One window's stay in the plan all the same, as the
+  // measure by which callers compare a sliced call with the unsliced one.
+  if (p->f32_cols) p->lanes = 1;
   p->lane_stride = off - p->off_a;
   for (int l = 1; l < p->lanes; ++l) take(p->lane_stride);
   // Similarity partials of the fused statistics + rehash pass (3 doubles per block), then {cos, decision}:
@@ -291,6 +294,7 @@ static si_status make_plan(const si_tensor5* x, const si_block_weights* w, const
   p->off_pe = take(p->pe ? (size_t)p->F * Dz * sizeof(float) : 0);
   // re-laid-out weights ([N, K]; fragment streams pad N to whole column tiles)
   auto wbytes = [&](size_t N, size_t K) {
+    if (p->f32_cols) return (size_t)0;  // read as they are
     if (!p->ring) return N * K * es;
     const RingShape rs = ring_shape(RingDims{p->Mmax, p->lanes}, (int)N, (int)K);
     return (size_t)rs.ncol * rs.tn * 32 * K * es;

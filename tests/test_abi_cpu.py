@@ -271,3 +271,18 @@ def test_windows_in_flight_follow_the_slice_count():
     assert _in_flight(x, w, None, B.SI_AXIS_HW, 12) == 2             # 8 slices
     assert _in_flight(x, w, None, B.SI_AXIS_HW, 8) == 3              # 12 slices
     assert _in_flight(x, w, None, B.SI_AXIS_F, 1) == 0               # invalid: temporal block along frames
+
+
+def test_fp32_block_in_one_kernel_holds_no_weights_and_one_window():
+    """It reads the parameters as they are and has no windows in memory: apart from what is derived from activations the
+    workspace holds the frame table only."""
+    lib = si.lib()
+    for pe in (0, 1):
+        x, w, _, _ = _descs(dtype=B.SI_F32, Cn=128, heads=2, dh=64, F=16, H=20, W=20)
+        w.add_sin_pe = pe
+        args = (C.byref(x), C.byref(w), None, B.SI_AXIS_HW, 25)   # 16 slices
+        assert lib.si_windows_in_flight(*args) == 1
+        assert lib.si_workspace_bytes(*args) - lib.si_live_activation_bytes(*args) == pe * 16 * 128 * 4
+    x, w, _, _ = _descs(dtype=B.SI_F32, Cn=320, heads=5, dh=64, groups=32, F=10, H=20, W=20)
+    staged = (C.byref(x), C.byref(w), None, B.SI_AXIS_HW, 400)    # a window large enough for the staged kernels
+    assert lib.si_workspace_bytes(*staged) - lib.si_live_activation_bytes(*staged) >= 18 * 320 * 320 * 4
