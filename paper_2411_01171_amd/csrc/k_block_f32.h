@@ -3,22 +3,23 @@
 //
 // A workgroup takes as many whole sequences (positions) as fill 16 TT token columns and keeps everything of
 // them in LDS, channel-major ([channel][token]), so a window has no intermediates in memory and nothing needs
-// to be ordered between windows: one grid covers them all.  The contractions run on v_mfma_f32_16x16x4_f32 (fp32
+// to be ordered between windows: a grid covers them all.  The contractions run on v_mfma_f32_16x16x4_f32 (fp32
 // operands, fp32 accumulation in k order): the weight is the row operand, read from the caller's [K, N] matrix
 // as it is (a lane's element (k, n): four 64-byte pieces per load), the tokens are the column operand, one
-// conflict-free LDS read of 64 consecutive floats.  The next 64 k-values of weight are loaded before the MFMAs
+// LDS read of 64 consecutive floats (TT = 1; with TT = 2 four pieces of 16, two of which share their banks).  The next 64 k-values of weight are loaded before the MFMAs
 // of the current ones, the first ones of the next contraction before the barriers in between.
 //
 // The results are those of the staged fp32 kernels bit for bit, so that a call's windows may take either: the matrix
 // instruction is a chain of fused multiply-adds in k order, as gemm_f32_kernel's and attn_valu_kernel's loops are, and
 // the sums of LayerNorm and softmax are added in layer_norm_kernel's and attn_valu_kernel's order.
 //
-// Whole calls, start (one launch per operator and window, 49 in the first row) -> this kernel:
-//   D 64, 8 frames of 8x8, B 1                  455 -> 26 us
-//   D 64, 16 frames of 20x20, B 2, 4 windows    492 -> 71 us
-//   D 320, 16 frames of 20x20, B 2, 4 windows  1995 -> 950 us
+// Whole calls, staged kernels (one launch per operator and window, 49 in the first row) -> this kernel:
+//   D 64, 8 frames of 8x8, B 1                  454 -> 26 us
+//   D 64, 16 frames of 20x20, B 2, 4 windows    494 -> 72 us
+//   D 128, 16 frames of 20x20, B 2, 4 windows   836 -> 175 us
+//   D 320, 16 frames of 20x20, B 2, 4 windows  1974 -> 960 us
 // Bound: small calls by the chain of some fifteen barriers and weight round trips (L2), large ones by the fp32
-// matrix rate (256 flop per clock and CU) and the weight stream, 64 D^2 bytes per 16 TT tokens.
+// matrix rate (256 flop per clock and CU) and the weight stream, 64 D^2 + 8 C D bytes per 16 TT tokens.
 #pragma once
 #include "k_norm.h"
 #include "si_common.h"
@@ -26,8 +27,8 @@
 namespace si {
 
 // Two instantiations per TT.  64 KiB of LDS and 8 wavefronts, so that two workgroups share a CU; else 16 wavefronts,
-// which is what one workgroup needs to keep weight loads in flight (12800 tokens: D = 64 63 us with 8, 87 us with 16;
-// D = 320 1128 us with 8, 945 us with 16; twice as many k-steps in flight per wavefront gain 0 .. 6 % at D >= 128
+// which is what one workgroup needs to keep weight loads in flight (the kernel alone on 12800 tokens: D = 64 63 us with 8,
+// 87 us with 16; D = 320 1128 us with 8, 945 us with 16; twice as many k-steps in flight per wavefront gain 0 .. 6 % at D >= 128
 // and lose 25 % on a call of 512 tokens).
 constexpr int kF32SmallFloats = 16384, kF32SmallThreads = 512;
 constexpr int kF32LdsFloats = 40960 - 512, kF32Threads = 1024;  // 160 KiB less the reduction scratch

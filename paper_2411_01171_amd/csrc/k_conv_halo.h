@@ -8,10 +8,11 @@
 // Wavefront (pair, ks) contracts the pair's 64 tokens over channels 16 ks .. +15 of every chunk: 7 KiB of
 // LDS reads for 10 MFMAs, where 32-token wavefronts would need 6 KiB for 5.  The two halves of a sum meet in LDS once,
 // after the last stage.  A stage is one kernel row (three taps) of a chunk: 42 KiB of weights and patch arrive one load
-// per wavefront and every other step, because a load blocks its wavefront while the address unit takes it (about 24
-// cycles per KiB and CU); behind the barrier all at once they cost a third of the time, with a 4-wavefront
-// workgroup (96 x 160 each) they stop the only wavefront of a SIMD (one tap 930 cycles instead of 880, of
-// which the MFMAs are 640).
+// per wavefront and every other step, because a load blocks its wavefront while the address unit takes it: all at once
+// behind the barrier they made the first of the calls below 2262 us instead of 2152, and with 4 wavefronts of 96 x 160,
+// where they stop the only wavefront of a SIMD, it took 2697.
+// One frame of 72 x 128 x 2, 320 channels, alone on the GPU: 50 us, of which the MFMAs of the 144 workgroups' 90 taps (640
+// cycles each) are 24; prologue, exchange and epilogue are outside the taps.
 // Measured (ring kernel -> this one): ResBlock of 320 channels on 72 x 128, 25 frames one at a time, 2450 -> 2240 us; 640
 // channels on 36 x 64, 16 frames two at a time, 1490 -> 1267 us; 640 channels doubled to 72 x 128, 12 frames, 1630 ->
 // 1394 us (1.0 -> 1.17 PFLOP/s).

@@ -1,5 +1,5 @@
-"""Matrix-core attention at every head dimension class and at ragged lengths, through the block forward, vs the
-CPU oracle: spatial self- and cross-attention on fragment operands, temporal attention of up to 32 frames."""
+"""Attention at every head dimension class and at ragged lengths, through the block forward, vs the CPU oracle: spatial
+self- and cross-attention, temporal attention of up to 32 frames."""
 import numpy as np
 import pytest
 
@@ -31,8 +31,8 @@ def _check(spec, ctx, slice_len, wq_scale=1.0):
     assert e["max_abs"] <= half_ulp + 6 * BRANCH_REL * float(np.std(ref - x)), (half_ulp, float(np.std(ref - x)))
 
 
-# head dimensions: one to eight 16-channel k-steps, odd and even counts of 8-channel pieces; D = 32 n runs on the
-# ring GEMMs (value tiles with swapped operands where H*W % 32 == 0), other widths on the row-major GEMM
+# head dimensions: one to sixteen 8-channel pieces, odd and even counts; D = 32 n runs on the ring GEMMs (attention output
+# in fragment order), other widths on the row-major GEMM
 @pytest.mark.parametrize("heads,d", [(8, 8), (4, 16), (3, 24), (4, 32), (4, 40), (2, 40), (4, 48), (2, 56), (4, 72), (2, 80), (2, 96), (2, 112), (1, 128)])
 @pytest.mark.parametrize("hw,M", [((8, 8), 1), ((5, 13), 33), ((12, 16), 64)])
 def test_spatial(heads, d, hw, M):
@@ -40,12 +40,12 @@ def test_spatial(heads, d, hw, M):
     _check(spec, wl.make_context(spec), 2)
 
 
-# lengths around the 32-key tiles, 64-key stages and 128-query tiles
+# lengths around the 16-key tiles, 64-key chunks and 128-query tiles; up to 32 positions run on the short kernel
 @pytest.mark.parametrize("P", [1, 31, 33, 63, 65, 97, 127, 129, 191, 225])
 @pytest.mark.parametrize("heads,d", [(4, 40), (2, 80)])
 def test_spatial_ragged_lengths(P, heads, d):
     spec = tiny_spec(wl.SPATIAL, B=1, C=64, F=2, H=1, W=P, heads=heads, dim_head=d, groups=8, M=P % 50 + 1, Cc=16, dtype="bf16")
-    _check(spec, wl.make_context(spec), 1, wq_scale=3.0)  # sharpened scores: the reference maximum moves between tiles
+    _check(spec, wl.make_context(spec), 1, wq_scale=3.0)  # sharpened scores: the running maximum moves between chunks
 
 
 @pytest.mark.parametrize("heads,d", [(8, 8), (4, 32), (2, 40), (4, 40), (2, 56), (2, 64), (2, 80), (2, 96), (1, 112), (2, 128)])
@@ -54,3 +54,18 @@ def test_temporal(heads, d, F):
     """5 x 7 positions in windows of 10: sequences that fill no workgroup, a ragged last window."""
     spec = tiny_spec(wl.TEMPORAL, B=2, C=96, F=F, H=5, W=7, heads=heads, dim_head=d, groups=8, pe=True, dtype="bf16")
     _check(spec, None, 10, wq_scale=2.0)
+
+
+@pytest.mark.parametrize("heads,d,hw,M", [(1, 40, (64, 64), 77), (2, 80, (48, 50), 200)])
+def test_spatial_long(heads, d, hw, M):
+    """Thousands of keys, tens of 64-key chunks, with scores sharp enough that the running maximum keeps moving."""
+    spec = tiny_spec(wl.SPATIAL, B=1, C=64, F=1, H=hw[0], W=hw[1], heads=heads, dim_head=d, groups=8, M=M, Cc=16, dtype="bf16")
+    _check(spec, wl.make_context(spec), 1, wq_scale=3.0)
+
+
+@pytest.mark.parametrize("heads,d", [(2, 40), (2, 64), (1, 128)])
+@pytest.mark.parametrize("F", [33, 64, 65, 130])
+def test_temporal_long(heads, d, F):
+    """Sequences past the short kernel: one 64-key chunk, several, a last one of one and of two keys."""
+    spec = tiny_spec(wl.TEMPORAL, B=1, C=96, F=F, H=3, W=5, heads=heads, dim_head=d, groups=8, pe=True, dtype="bf16")
+    _check(spec, None, 4, wq_scale=2.0)

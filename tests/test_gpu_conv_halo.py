@@ -1,6 +1,6 @@
 """The 3x3 convolution kernel that keeps a patch of source tokens in LDS, where it can go wrong: tiles that straddle
-images and end inside the last one, odd maps (no 32-token blocks), the widest map it takes (twelve 64-token blocks per
-patch), one channel chunk and several, doubled maps -- against the float64 oracle."""
+images and end inside the last one, odd maps (no 32-token blocks), the widest maps it takes (ten to twelve 64-token
+blocks per patch), one channel chunk and several, one column tile and two, doubled maps -- against the float64 oracle."""
 import numpy as np
 import pytest
 
@@ -26,7 +26,13 @@ def test_same_map(shape, c_out):
                    oracle.resblock_forward_ref(x, w, spec, temb), x)
 
 
-@pytest.mark.parametrize("shape", [(1, 160, 1, 73, 130), (4, 160, 1, 49, 49)])
+@pytest.mark.parametrize("shape", [
+    (1, 160, 1, 73, 130),
+    (4, 160, 1, 49, 49),
+    (1, 160, 1, 41, 200),          # ten 64-token blocks per patch
+    (1, 160, 1, 34, 240),          # twelve
+    (1, 320, 1, 46, 90),           # two column tiles
+])
 def test_doubled_map(shape):
     x, w, b = _inputs(*shape, seed=sum(shape))
     check_resample(f"halo up {shape}", _run(x, w, b, "up", 1), oracle.upsample_ref(x, w, b))
