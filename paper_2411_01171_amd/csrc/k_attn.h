@@ -33,8 +33,9 @@ struct AttnArgs {
 // One wavefront serves QB queries of one (sequence, head): in the score phase
 // each lane owns one key of a 64-key chunk and forms QB dot products; in the
 // value phase each lane owns channels lane and lane+64 (d <= 128).  Exact expf,
-// fp32 throughout: this is the path of the fp32 block (16-bit storage takes
-// attn_f32mma_kernel, the same arithmetic on fp32 matrix instructions).
+// fp32 throughout: this is the path of the staged fp32 block (16-bit storage takes
+// attn_short_kernel and attn_f32mma_kernel, the same arithmetic on fp32 matrix
+// instructions).
 template <typename T, int QB>
 __global__ __launch_bounds__(256) void attn_valu_kernel(AttnArgs a) {
   __shared__ float qs[4][QB][128];
