@@ -13,12 +13,14 @@
 //
 // One workgroup = 4 wavefronts x 32 queries (two column tiles, so that a key / value operand serves two MFMAs) of one
 // (sequence, head).  Chunks of 64 keys pass through LDS as fp32 operands, [operand][lane][4 steps]: one 16-byte read
-// of consecutive lanes per four steps.  The next chunk's rows are loaded while the current one is contracted.
+// of consecutive lanes per four steps; the values' channels lie exclusive-ored with the key group, so that a store of
+// one channel of many keys spreads over half of the banks instead of an eighth.  The next chunk's rows are loaded while the current one is contracted.
 //
 // Bound by the fp32 matrix rate, 256 flop per clock and CU, and the exponentials, which do not overlap with it on a
 // SIMD: at 40 channels 176 MFMAs of 32 cycles (channels padded to 48 in the second product) and 34 expf of some 14
 // instructions per 64 keys x 32 queries.  Three wavefronts per SIMD up to 40 channels, as many as the registers allow
-// (16 frames of 64 x 64 positions, 8 heads of 40, whole call: 10.07 -> 9.82 ms; attn_valu_kernel 66.7 ms).
+// (16 frames of 64 x 64 positions, 8 heads of 40, whole call: 10.07 -> 9.82 ms, 9.28 with the values spread; attn_valu_kernel 66.7 ms.  Self-attention of
+// one frame, 43 GFLOP: 4390 -> 498 us).
 #pragma once
 #include "k_attn.h"
 
@@ -68,12 +70,12 @@ __global__ __launch_bounds__(256, D8 <= 5 ? 3 : D8 <= 10 ? 2 : 1) void attn_f32m
         if (id >= NG) continue;
         const int t = key / 16, j = key % 16 / 4, kg = key % 4;
         float* kd = reinterpret_cast<float*>(kl + (t * KQ + c8 / 2) * kWave + 4 * kg + j) + 2 * (c8 % 2);
-        float* vd = reinterpret_cast<float*>(vl + (t * DB + c8 / 2) * kWave + 16 * kg + 8 * (c8 % 2)) + j;
+        float* vd = reinterpret_cast<float*>(vl + (t * DB + c8 / 2) * kWave + 16 * kg) + j;
 #pragma unroll
         for (int e = 0; e < 4; ++e)
           *reinterpret_cast<float2*>(kd + 16 * 4 * e) = make_float2(half(kr[i][e / 2], e & 1), half(kr[i][2 + e / 2], e & 1));
 #pragma unroll
-        for (int e = 0; e < 8; ++e) vd[4 * e] = half(vr[i][e / 2], e & 1);
+        for (int e = 0; e < 8; ++e) vd[4 * ((8 * (c8 % 2) + e) ^ 2 * kg)] = half(vr[i][e / 2], e & 1);
       }
     };
     load(0);
@@ -164,7 +166,7 @@ __global__ __launch_bounds__(256, D8 <= 5 ? 3 : D8 <= 10 ? 2 : 1) void attn_f32m
         if (kc + 16 * t < a.Nk) {
           f32x4_t vq[DB];
 #pragma unroll
-          for (int b = 0; b < DB; ++b) vq[b] = *reinterpret_cast<const f32x4_t*>(vl + (t * DB + b) * kWave + lane);
+          for (int b = 0; b < DB; ++b) vq[b] = *reinterpret_cast<const f32x4_t*>(vl + (t * DB + b) * kWave + (lane ^ 2 * g));
 #pragma unroll
           for (int j = 0; j < 4; ++j)
 #pragma unroll
