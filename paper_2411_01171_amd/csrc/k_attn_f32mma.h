@@ -14,13 +14,14 @@
 // One workgroup = 4 wavefronts x 32 queries (two column tiles, so that a key / value operand serves two MFMAs) of one
 // (sequence, head).  Chunks of 64 keys pass through LDS as fp32 operands, [operand][lane][4 steps]: one 16-byte read
 // of consecutive lanes per four steps; the values' channels lie exclusive-ored with the key group, so that a store of
-// one channel of many keys spreads over half of the banks instead of an eighth.  The next chunk's rows are loaded while the current one is contracted.
+// one channel of many keys spreads over half of the banks instead of an eighth.  The next chunk's rows are loaded while
+// the current one is contracted.
 //
-// Bound by the fp32 matrix rate, 256 flop per clock and CU, and the exponentials, which do not overlap with it on a
-// SIMD: at 40 channels 176 MFMAs of 32 cycles (channels padded to 48 in the second product) and 34 expf of some 14
-// instructions per 64 keys x 32 queries.  Three wavefronts per SIMD up to 40 channels, as many as the registers allow
-// (16 frames of 64 x 64 positions, 8 heads of 40, whole call: 10.07 -> 9.82 ms, 9.28 with the values spread; attn_valu_kernel 66.7 ms.  Self-attention of
-// one frame, 43 GFLOP: 4390 -> 498 us).
+// Bound by the fp32 matrix rate, 256 flop per clock and CU, and the exponentials, which overlap with it in part only:
+// at 40 channels 176 MFMAs of 32 cycles (channels padded to 48 in the second product) and 34 expf of some 14
+// instructions per 64 keys x 32 queries.  Three wavefronts per SIMD up to 40 channels, as many as the registers allow.
+// Self-attention of one 64 x 64 frame, 8 heads of 40, two sequences (43 GFLOP): attn_valu_kernel 4390 us, this kernel 542
+// with the values in channel order, 498 as it is; 16 such frames, whole call, 66.7 -> 9.28 ms.
 #pragma once
 #include "k_attn.h"
 

@@ -126,7 +126,10 @@ static void conv_column_tiles(int O, int64_t rows_in_flight, int* TN, int* ncol)
 // those in flight, as one window of two frames or as two windows.  Measured (ring kernel -> this one, calls of one frame
 // per window): 64 tiles x 2 in flight 606 -> 563 us (320 channels, 64 x 64, 8 frames) and 716 -> 573 us (1280
 // channels doubled to 32 x 32); 36 x 2: 864 -> 1130 us, 40 x 2: 1049 -> 1272 us, 72 x 1: 887 -> 1099 us: half of the
-// 256 CUs have to have a workgroup.  Maps wider than the patch buffer stay on the ring kernel too.
+// 256 CUs have to have a workgroup.  Over 498 calls of 66 .. 300 tiles, 2 .. 25 frames in windows of 1 .. 8, the ring
+// kernel takes 1.0 .. 1.28 times as long at 320 and more channels (mean 1.05 .. 1.16, one doubled map 0.96), 0.95 .. 1.14
+// times at 32 and 160 channels, which have few chunks to spread the prologue over.  Only the 160-column form is built:
+// other output widths (256, 512), and maps wider than the patch buffer, stay on the ring kernel.
 constexpr int kHaloMin = 128, kHaloMaxBlocks = 12;
 static int halo_plan(int B, int F, int O, int H, int W, int Wi, int mode) {
   const int64_t tiles = ((int64_t)B * H * W + kHaloTokens - 1) / kHaloTokens * (O / (32 * kHaloTN)), nblk = halo_blocks(W, Wi, mode);
