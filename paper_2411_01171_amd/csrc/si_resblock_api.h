@@ -2,6 +2,7 @@
 // workspace layout, the slice loop over frame windows and the kernel launches.  Part of the
 // translation unit si_api.hip (uses its stage timing, alignment and overlap helpers).
 #pragma once
+#include "k_conv_down.h"
 #include "k_conv_halo.h"
 
 #ifndef SI_RES_LANES3_MIN
@@ -307,10 +308,26 @@ static si_status run_resblock(const ResPlan& p, const si_tensor5* x, const si_re
 
 struct ResamplePlan {
   int B, C, F, Hi, Wi, Ho, Wo, mode, TN, ncol, halo;
+  bool down;  // conv_down_kernel: every window in one launch, no operand buffer
   int64_t Pi, Po, slice_len, Mi_max;
   int lanes;
   size_t lane_stride, off_a, off_w, weights_bytes, total_bytes;
 };
+
+// Whether a DownSample runs on conv_down_kernel: channels in whole column tiles of 320 (the only form built; 256- and
+// 512-channel networks stay on the ring kernel), patches that fit LDS (maps up to some 180 wide), four positions to load.
+// Measured over 320 .. 1280 channels, 9 x 11 .. 72 x 128 maps, 6 .. 25 frames, windows of 1 and 2: 1.3 .. 2.9 times the ring
+// kernel's speed, the small and odd maps included.
+static bool down_fits(const ResamplePlan& p) {
+  const int64_t ntile = (p.Po + kDownTokens - 1) / kDownTokens, nwg = (int64_t)p.B * p.F * ntile * (p.C / (32 * kDownTN));
+  if (p.C % (32 * kDownTN) || p.Pi < 4 || nwg >= 1 << 30) return false;
+  for (int64_t t = 0; t < ntile; ++t) {
+    int s0, n;
+    down_patch((int)(t * kDownTokens), (int)((t + 1) * kDownTokens < p.Po ? (t + 1) * kDownTokens : p.Po) - 1, p.Wi, p.Wo, &s0, &n);
+    if (n > 4 * kDownGroups) return false;
+  }
+  return true;
+}
 
 static si_status make_resample_plan(const si_tensor5* x, int32_t kind, int64_t slice_len, ResamplePlan* p) {
   if (!x) return SI_ERR_NULL;
@@ -331,9 +348,13 @@ static si_status make_resample_plan(const si_tensor5* x, int32_t kind, int64_t s
   if ((double)p->Mi_max * p->C * 2.0 + 4096.0 >= 4294967296.0) return SI_ERR_SHAPE;  // 32-bit operand offsets
   if ((int64_t)p->B * p->slice_len * p->Po >= (1LL << 31) / 16) return SI_ERR_SHAPE;
   const int64_t n_slices = (p->F + p->slice_len - 1) / p->slice_len;
-  p->lanes = n_slices >= 8 ? 2 : 1;
+  p->down = p->mode == kConvStride2 && down_fits(*p);
+  p->lanes = n_slices >= 8 && !p->down ? 2 : 1;
   p->halo = p->mode == kConvNearestUp ? halo_plan(p->B, p->F, p->C, p->Ho, p->Wo, p->Wi, p->mode) : 0;
-  if (p->halo) {
+  if (p->down) {
+    p->TN = kDownTN;
+    p->ncol = p->C / (32 * kDownTN);
+  } else if (p->halo) {
     p->TN = kHaloTN;
     p->ncol = p->C / (32 * kHaloTN);
   } else conv_column_tiles(p->C, ((int64_t)p->B * p->slice_len * p->Po + 127) / 128 * p->lanes, &p->TN, &p->ncol);
@@ -343,7 +364,7 @@ static si_status make_resample_plan(const si_tensor5* x, int32_t kind, int64_t s
     off = align_up(off + bytes, 256);
     return o;
   };
-  p->off_a = take(kActZeroBytes + (size_t)((p->Mi_max + 31) / 32 * 32) * p->C * 2);
+  p->off_a = take(p->down ? 0 : kActZeroBytes + (size_t)((p->Mi_max + 31) / 32 * 32) * p->C * 2);
   p->lane_stride = off - p->off_a;
   if (p->lanes == 2) take(p->lane_stride);
   const size_t act_end = off;
@@ -364,8 +385,17 @@ static si_status run_resample(const ResamplePlan& p, const si_tensor5* x, const 
     const int64_t elems = (int64_t)p.ncol * 9 * (C / 32) * 2 * p.TN * 512;
     unsigned* z0 = reinterpret_cast<unsigned*>(ws + p.off_a);
     pack_conv_kernel<false><<<(unsigned)((elems + 255) / 256), 256, 0, st0>>>(static_cast<const bf16*>(w_conv), wf, C, C, p.TN,
-                                                                             p.ncol, z0, p.lanes, (int64_t)p.lane_stride);
+                                                                             p.ncol, z0, p.down ? 0 : p.lanes, (int64_t)p.lane_stride);
     SI_CHECK_LAUNCH();
+  }
+  if (p.down) {
+    StageScope scope("conv_down", st0);
+    ConvDownArgs a{X, OUT, static_cast<const bf16*>(b_conv), reinterpret_cast<const char*>(wf), C, C, p.F, p.Wi, p.Hi, (int)p.Pi,
+                   p.Wo, (int)p.Po, (int)((p.Po + kDownTokens - 1) / kDownTokens), p.ncol, 0};
+    a.nwg = p.B * p.F * a.ntile * a.ncol;
+    conv_down_kernel<<<(unsigned)((a.nwg + 7) / 8 * 8), 512, 0, st0>>>(a);
+    SI_CHECK_LAUNCH();
+    return SI_OK;
   }
   AuxStream* aux = nullptr;
   const int lanes = g_timing ? 1 : p.lanes;
