@@ -314,12 +314,15 @@ __global__ __launch_bounds__(WS ? 512 : 256, (WS && TM * TN > 2) ? 1 : 2) void r
     // whole 32-column blocks go to the epilogue's block form (every lane takes part in its exchange)
     if (a.O % 32 == 0) {
 #pragma unroll
-      for (int j = 0; j < TM; ++j)
+      for (int i = 0; i < TN; ++i) {
+        const int n0 = (col * TN + i) * 32;
+        if (n0 < a.O) {
+          typename Epi::Ahead ahead;
+          epi.request(ahead, n0, half);
 #pragma unroll
-        for (int i = 0; i < TN; ++i) {
-          const int n0 = (col * TN + i) * 32;
-          if (n0 < a.O) epi.block32(tok[j], tok[j] < a.M, n0, acc[i][j], half);
+          for (int j = 0; j < TM; ++j) epi.block32(tok[j], tok[j] < a.M, n0, acc[i][j], half, ahead);
         }
+      }
       return;
     }
   }

@@ -106,11 +106,26 @@ struct EpiStoreKVt {
 template <typename T, bool FRAG = false>
 struct EpiResidual {
   static constexpr bool kRows8 = false;
+  static constexpr bool kResidual = sizeof(T) == 2;
   float* h;
   int64_t ld;
   const T* bias;
   int accumulate;
   T* copy;
+  __device__ __forceinline__ void store_copy(int64_t m, int n0, const float4& o) const {
+    const float ov[4] = {o.x, o.y, o.z, o.w};
+    if constexpr (sizeof(T) == 2) {
+      typedef _Float16 f16x4_t __attribute__((ext_vector_type(4)));
+      f16x4_t c4;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) c4[i] = (_Float16)__builtin_amdgcn_fmed3f(ov[i], -65504.f, 65504.f);
+      *reinterpret_cast<f16x4_t*>(copy + (FRAG ? act_offset(m, n0, (int)ld) : m * ld + n0)) = c4;
+    } else {
+      T* c = copy + m * ld + n0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) c[i] = from_float<T>(ov[i]);
+    }
+  }
   __device__ __forceinline__ void operator()(int64_t m, int n0, const float (&v)[4]) const {
     float4* p = reinterpret_cast<float4*>(h + m * ld + n0);
     float4 o = accumulate ? *p : make_float4(0.f, 0.f, 0.f, 0.f);
@@ -119,20 +134,7 @@ struct EpiResidual {
     o.z += v[2] + param_or(bias, n0 + 2, 0.f);
     o.w += v[3] + param_or(bias, n0 + 3, 0.f);
     *p = o;
-    if (copy) {
-      const float ov[4] = {o.x, o.y, o.z, o.w};
-      if constexpr (sizeof(T) == 2) {
-        typedef _Float16 f16x4_t __attribute__((ext_vector_type(4)));
-        f16x4_t c4;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) c4[i] = (_Float16)__builtin_amdgcn_fmed3f(ov[i], -65504.f, 65504.f);
-        *reinterpret_cast<f16x4_t*>(copy + (FRAG ? act_offset(m, n0, (int)ld) : m * ld + n0)) = c4;
-      } else {
-        T* c = copy + m * ld + n0;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) c[i] = from_float<T>(ov[i]);
-      }
-    }
+    if (copy) store_copy(m, n0, o);
   }
 };
 
@@ -155,18 +157,25 @@ struct EpiGeglu {
   // GELU is the polynomial of the register-resident kernels.  Called by every lane of the wavefront
   // (the exchange needs them all); rows past the end are not stored.
   static constexpr bool kBlock32 = FRAG && sizeof(T) == 2;
-  __device__ __forceinline__ void block32(int64_t m, bool mvalid, int n0, const f32x16_t& acc, int half) const {
+  // The block's biases are requested apart, so that a kernel can have all of its blocks' in flight at once.
+  struct Ahead {
+    unsigned v[4], g[4];
+  };
+  __device__ __forceinline__ void request(Ahead& q, int n0, int half) const {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int j = (n0 >> 1) + 4 * k + 2 * half;  // even, the vector 4-byte aligned: two adjacent 16-bit values per load
+      q.v[k] = b1 ? *reinterpret_cast<const unsigned*>(b1 + j) : 0u;
+      q.g[k] = b1 ? *reinterpret_cast<const unsigned*>(b1 + inner + j) : 0u;
+    }
+  }
+  __device__ __forceinline__ void block32(int64_t m, bool mvalid, int n0, const f32x16_t& acc, int half, const Ahead& ahead) const {
     const int j0 = n0 >> 1;  // first of the block's 16 output channels
     unsigned d[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const int j = j0 + 4 * q + 2 * half;
-      float bv0 = 0.f, bv1 = 0.f, bg0 = 0.f, bg1 = 0.f;
-      if (b1) {  // two adjacent 16-bit values per load (j is even, the vector 4-byte aligned)
-        const unsigned wv = *reinterpret_cast<const unsigned*>(b1 + j), wg = *reinterpret_cast<const unsigned*>(b1 + inner + j);
-        bv0 = __uint_as_float(wv << 16); bv1 = __uint_as_float(wv & 0xffff0000u);
-        bg0 = __uint_as_float(wg << 16); bg1 = __uint_as_float(wg & 0xffff0000u);
-      }
+      const float bv0 = __uint_as_float(ahead.v[q] << 16), bv1 = __uint_as_float(ahead.v[q] & 0xffff0000u);
+      const float bg0 = __uint_as_float(ahead.g[q] << 16), bg1 = __uint_as_float(ahead.g[q] & 0xffff0000u);
       const float a0 = (acc[4 * q + 0] + bv0) * gelu_poly(acc[4 * q + 1] + bg0);
       const float a1 = (acc[4 * q + 2] + bv1) * gelu_poly(acc[4 * q + 3] + bg1);
       d[q] = (unsigned)float_to_bf16_bits(a0) | ((unsigned)float_to_bf16_bits(a1) << 16);

@@ -23,6 +23,7 @@
 #include "k_attn_mfma.h"
 #include "k_conv.h"
 #include "k_gemm.h"
+#include "k_gemm_wide.h"
 #include "k_norm.h"
 #include "si_common.h"
 
@@ -103,6 +104,11 @@ static RingShape ring_shape(RingDims d, int N, int K) {
     if (rows128 * ((N + 63) / 64) > 256 && rows128 * nc3 <= 256 && rows128 * nc3 > 160 && (int64_t)nc3 * 96 * 10 <= (int64_t)N * 11)
       return RingShape{3, nc3};
   }
+  // gemm_160_kernel (k_gemm_wide.h) needs a workgroup for three quarters of the CUs, over the windows in flight, to beat narrower
+  // tiles on the ring kernel, however many more those are.  Per launch alone, narrow -> 160 (us): N = K = 640 on 7000 tokens (220
+  // workgroups) 18.5 -> 15.2, K = 2560 41 -> 32; N = K = 1280 on 2048 tokens (128) 17.2 -> 18.4, K = 5120 37 -> 44.  N = K = 640 on
+  // 2048 tokens, 64 workgroups, 9 -> 12, but with three windows in flight (192 of 256 CUs) the block of them 1375 -> 1341.
+  if (K % 64 == 0 && N % 160 == 0 && (d.Mmax + 127) / 128 * (N / 160) * d.lanes >= 190) return RingShape{5, N / 160};
   const int64_t rows = (d.Mmax + 127) / 128 * (K > 512 ? d.lanes : 1);
   const int min_wg = K > 512 ? 330 : 400;
   RingShape best{1, (N + 31) / 32};
@@ -422,6 +428,33 @@ static si_status launch_gemm_ring(const char* stage, const void* act, const void
   ConvArgs a{static_cast<const char*>(act), static_cast<const char*>(wf), M, K, N, 1, 1, rs.ncol,
              (int)((big ? rows2 : (M + 127) / 128) * rs.ncol), 1, 1, kConvSame, 1,
              M < N ? 1 : 0};  // the smaller operand is the one every XCD streams
+  // 160-column tiles: gemm_160_kernel.  ff1 in tiles of 256 x 320 where those occupy seven eighths of the CUs, one each (10240
+  // columns on 2048 tokens: 512 tiles of 256 x 160 took 61 us, 256 of these 47), else as before.  Other GEMMs with three slots,
+  // one workgroup per CU, or, where there is a second one for it and the epilogue needs no more, two slots and two workgroups
+  // (q/k/v at 640 channels on 7000 tokens 32 -> 28.7 us).
+  if (rs.tn == 5 && N % 160 == 0 && K % 64 == 0) {
+    auto launch = [&](auto wc, auto tm, auto slots) {
+      constexpr int WC = decltype(wc)::value, TM = decltype(tm)::value;
+      a.ncol = N / (160 * WC);
+      a.ntiles = (int)((M + 128 * TM - 1) / (128 * TM) * a.ncol);
+      gemm_160_kernel<WC, TM, decltype(slots)::value, F16, Epi><<<(unsigned)((a.ntiles + 7) / 8 * 8), 256 * WC, 0, st>>>(a, epi);
+    };
+    using I1 = std::integral_constant<int, 1>;
+    using I2 = std::integral_constant<int, 2>;
+    if constexpr (epi_block32<Epi>::value) {
+      if (N % 320 == 0 && rows2 * (N / 320) * Mmax.lanes >= 224) {
+        launch(I2(), I2(), I2());
+        SI_CHECK_LAUNCH();
+        return SI_OK;
+      }
+    } else {
+      using Slots = std::integral_constant<int, epi_residual<Epi>::value ? 3 : 2>;
+      if ((M + 127) / 128 * (N / 160) <= 256) launch(I1(), I1(), std::integral_constant<int, 3>());
+      else launch(I1(), I1(), Slots());
+      SI_CHECK_LAUNCH();
+      return SI_OK;
+    }
+  }
   const unsigned grid = (unsigned)((a.ntiles + 7) / 8 * 8);
   // Narrow tiles (64 or 32 columns: the N = D projections and ff2) run wavefront-specialised: their
   // launches have one or two workgroups per CU, too few to hide a workgroup's load issue behind
