@@ -197,10 +197,55 @@ __global__ __launch_bounds__(256) void window_to_tokens_kernel(const T* __restri
   }
 }
 
+// What a thread of a whole 64 x 64 (position x channel) slice-in tile reads: four positions of channels ct + tid / 16 + 16 i,
+// all requested before the first is used (2048 tokens x 640 channels 8.0 -> 5.3 us; with one after the other a tile waited for memory four
+// times).
+// Positions lie at any 2-byte alignment; the loads are 8 bytes wide all the same.
+struct SliceTile {
+  uint2 raw[4];
+  float mean[4], rstd[4], ga[4], be[4];
+  __device__ __forceinline__ float x(int i, int j) const {
+    const unsigned u = j < 2 ? raw[i].x : raw[i].y;
+    return __uint_as_float(j & 1 ? u & 0xffff0000u : u << 16);
+  }
+};
+template <typename T>
+__device__ __forceinline__ SliceTile load_slice_tile(const T* x, const float* stats, const T* gamma, const T* beta, const Window& w, int b,
+                                                     int f, int pt, int ct, int ng) {
+  SliceTile t;
+  const int c0 = ct + (int)threadIdx.x / 16;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    __builtin_memcpy(&t.raw[i], x + (((int64_t)b * w.C + c0 + 16 * i) * w.F + f) * w.P + w.p0 + pt + threadIdx.x % 16 * 4, 8);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    t.mean[i] = 0.f;
+    t.rstd[i] = t.ga[i] = 1.f;
+    t.be[i] = 0.f;
+  }
+  if (stats) {
+    const float2* st = reinterpret_cast<const float2*>(stats) + ((int64_t)b * w.F + f) * w.G;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float2 s = st[(c0 + 16 * i) / ng];
+      t.mean[i] = s.x;
+      t.rstd[i] = s.y;
+    }
+  }
+  if (gamma) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) t.ga[i] = to_float(gamma[c0 + 16 * i]);
+  }
+  if (beta) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) t.be[i] = to_float(beta[c0 + 16 * i]);
+  }
+  return t;
+}
+
 // Slice-in for bf16 storage: the normalised value (bounded by construction) is kept as fp16, the
 // operand type of proj_in on this path -- three more significand bits than bf16 for the same bytes.
-// 8-byte reads along positions (when the frame size and the window start are multiples of 4
-// positions), 16-byte writes of 8 channels.  C % 8 == 0; row m holds C values, or (FRAG) the
+// 8-byte reads along positions, 16-byte writes of 8 channels.  C % 8 == 0; row m holds C values, or (FRAG) the
 // buffer is in the ring kernels' fragment order.
 template <bool FRAG>
 __global__ __launch_bounds__(256) void window_to_tokens_f16_kernel(const bf16* __restrict__ x, const float* __restrict__ stats,
@@ -211,35 +256,32 @@ __global__ __launch_bounds__(256) void window_to_tokens_f16_kernel(const bf16* _
   const int b = bf / w.Fw, fl = bf % w.Fw, f = w.f0 + fl;
   const int pt = blockIdx.x * 64, ct = blockIdx.y * 64;
   const int ng = w.C / w.G;
-  const bool vec_ok = (w.P % 4 == 0) && (w.p0 % 4 == 0);
+  if (pt + 64 <= w.Pw && ct + 64 <= w.C) {
+    // a whole tile, any alignment: everything is requested before anything is used
+    const SliceTile t = load_slice_tile<bf16>(x, stats, gamma, beta, w, b, f, pt, ct, ng);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int id = threadIdx.x + i * 256, cl = id / 16, pq = (id % 16) * 4;
-    const int c = ct + cl, pl = pt + pq;
-    float v[4] = {0.f, 0.f, 0.f, 0.f};
-    if (c < w.C && pl < w.Pw) {
-      const int g = c / ng;
-      const float mean = stats[(((int64_t)b * w.F + f) * w.G + g) * 2 + 0];
-      const float rstd = stats[(((int64_t)b * w.F + f) * w.G + g) * 2 + 1];
-      const float ga = param_or(gamma, c, 1.f), be = param_or(beta, c, 0.f);
-      const bf16* src = x + (((int64_t)b * w.C + c) * w.F + f) * w.P + w.p0 + pl;
-      float xv[4] = {0.f, 0.f, 0.f, 0.f};
-      if (vec_ok && pl + 3 < w.Pw) {
-        const uint2 raw = *reinterpret_cast<const uint2*>(src);
-        xv[0] = __uint_as_float(raw.x << 16);
-        xv[1] = __uint_as_float(raw.x & 0xffff0000u);
-        xv[2] = __uint_as_float(raw.y << 16);
-        xv[3] = __uint_as_float(raw.y & 0xffff0000u);
-      } else {
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) tile[threadIdx.x / 16 + 16 * i][threadIdx.x % 16 * 4 + j] = (t.x(i, j) - t.mean[i]) * t.rstd[i] * t.ga[i] + t.be[i];
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int id = threadIdx.x + i * 256, cl = id / 16, pq = (id % 16) * 4;
+      const int c = ct + cl, pl = pt + pq;
+      float v[4] = {0.f, 0.f, 0.f, 0.f};
+      if (c < w.C && pl < w.Pw) {
+        const int g = c / ng;
+        const float mean = stats[(((int64_t)b * w.F + f) * w.G + g) * 2 + 0];
+        const float rstd = stats[(((int64_t)b * w.F + f) * w.G + g) * 2 + 1];
+        const float ga = param_or(gamma, c, 1.f), be = param_or(beta, c, 0.f);
+        const bf16* src = x + (((int64_t)b * w.C + c) * w.F + f) * w.P + w.p0 + pl;
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-          if (pl + j < w.Pw) xv[j] = to_float(src[j]);
+          if (pl + j < w.Pw) v[j] = (to_float(src[j]) - mean) * rstd * ga + be;  // same expression as window_to_tokens_kernel
       }
 #pragma unroll
-      for (int j = 0; j < 4; ++j) v[j] = (xv[j] - mean) * rstd * ga + be;  // same expression as window_to_tokens_kernel
+      for (int j = 0; j < 4; ++j) tile[cl][pq + j] = v[j];
     }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) tile[cl][pq + j] = v[j];
   }
   __syncthreads();
 #pragma unroll
@@ -333,24 +375,27 @@ __global__ __launch_bounds__(256) void layer_norm_kernel(const float* __restrict
 // consecutive rows per workgroup.  The eight normalised rows meet in LDS, and the workgroup writes
 // them as whole 128-byte pieces of the fragment-order buffer (8 tokens x the 16 bytes of one
 // 8-channel granule) instead of 16-byte pieces per row; gain and shift are read four at a time.
-// Same arithmetic per element as layer_norm_kernel.
+// Same arithmetic per element as layer_norm_kernel.  Bound by latency: with registers for 2048 columns whatever the row two
+// wavefronts per SIMD were resident; for 640 columns (NQ = 3) 7000 rows take 15.5 -> 9.2 us, 2.9 TB/s.
+// NQ: float4 pieces of a row per lane, D <= 256 NQ.
+template <int NQ>
 __global__ __launch_bounds__(512) void layer_norm_rows8_kernel(const float* __restrict__ h, bf16* __restrict__ a, int64_t M, int D,
                                                                const bf16* __restrict__ gamma, const bf16* __restrict__ beta, float eps,
                                                                const float* __restrict__ pe, int Pw, int Fw, int f0) {
-  constexpr int LDR = 2048 + 8;  // 16-bit elements per LDS row: 16-byte aligned rows that rotate over the banks
+  constexpr int LDR = 256 * NQ + 8;  // 16-bit elements per LDS row: 16-byte aligned rows that rotate over the banks
   __shared__ __attribute__((aligned(16))) unsigned short tile[8][LDR];
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
   const int64_t m0 = (int64_t)blockIdx.x * 8, m = m0 + wave;
   if (m < M) {
     const float4* row = reinterpret_cast<const float4*>(h + m * D);
     const int nv = D / 4;
-    float4 r[8];
-    uint2 gr[8], br[8];  // gain and shift are requested together with the row: their latency hides behind the two sums
+    float4 r[NQ];
+    uint2 gr[NQ], br[NQ];  // gain and shift are requested together with the row: their latency hides behind the two sums
     const float* perow = pe ? pe + (int64_t)(f0 + (int)((m / Pw) % Fw)) * D : nullptr;
-    float4 pr[8];
+    float4 pr[NQ];
     float s = 0.f;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
+    for (int i = 0; i < NQ; ++i) {
       const int v = lane + i * kWave;
       if (v < nv) {
         r[i] = row[v];
@@ -360,14 +405,14 @@ __global__ __launch_bounds__(512) void layer_norm_rows8_kernel(const float* __re
       }
     }
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
+    for (int i = 0; i < NQ; ++i) {
       const int v = lane + i * kWave;
       if (v < nv) s += (r[i].x + r[i].y) + (r[i].z + r[i].w);
     }
     const float mean = wave_sum(s) / (float)D;
     float q = 0.f;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
+    for (int i = 0; i < NQ; ++i) {
       const int v = lane + i * kWave;
       if (v < nv) {
         const float dx = r[i].x - mean, dy = r[i].y - mean, dz = r[i].z - mean, dw = r[i].w - mean;
@@ -376,7 +421,7 @@ __global__ __launch_bounds__(512) void layer_norm_rows8_kernel(const float* __re
     }
     const float rstd = rsqrtf(wave_sum(q) / (float)D + eps);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
+    for (int i = 0; i < NQ; ++i) {
       const int v = lane + i * kWave;
       if (v < nv) {
         const float in[4] = {r[i].x, r[i].y, r[i].z, r[i].w};

@@ -503,6 +503,15 @@ static void head_dispatch(int d, Fn f) {
   }
 }
 
+// Calls f(integral_constant<n>) for n = 1 .. 8.
+template <int N = 1, class Fn>
+static void row_dispatch(int n, Fn f) {
+  if constexpr (N <= 8) {
+    if (n == N) f(std::integral_constant<int, N>());
+    else row_dispatch<N + 1>(n, f);
+  }
+}
+
 // o_frag (16-bit storage): 0, or o is a fragment-order buffer of that many channels per token.  Rows and head columns
 // of q, k and v are 16-byte pieces throughout (D and d are multiples of 8, the buffers 256-byte aligned).
 template <typename T>
@@ -578,7 +587,9 @@ static si_status launch_layer_norm(const char* stage, const float* h, T* a, int6
         case 1280: layer_norm_frag_kernel<40><<<wgs, 64, 0, st>>>(h, ap, M, gp, bp, eps, pe, Pw, Fw, f0); break;
         default:
           if (D % 8 == 0 && D <= 2048 && (!g || aligned16(g)) && (!b || aligned16(b)))
-            layer_norm_rows8_kernel<<<wgs, 512, 0, st>>>(h, ap, M, D, gp, bp, eps, pe, Pw, Fw, f0);
+            row_dispatch((D + 255) / 256, [&](auto nq) {
+              layer_norm_rows8_kernel<nq.value><<<wgs, 512, 0, st>>>(h, ap, M, D, gp, bp, eps, pe, Pw, Fw, f0);
+            });
           else
             layer_norm_kernel<T, sizeof(T) == 2><<<blocks, 256, 0, st>>>(h, a, M, D, static_cast<const T*>(g), static_cast<const T*>(b),
                                                                          eps, pe, Pw, Fw, f0);
