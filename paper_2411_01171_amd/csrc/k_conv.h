@@ -84,6 +84,92 @@ struct epi_block32 : std::false_type {};
 template <class Epi>
 struct epi_block32<Epi, std::enable_if_t<Epi::kBlock32>> : std::true_type {};
 
+template <class Epi, class = void>
+struct epi_residual : std::false_type {};
+template <class Epi>
+struct epi_residual<Epi, std::enable_if_t<Epi::kResidual>> : std::true_type {};
+
+template <class Epi, class = void>
+struct epi_slice_out : std::false_type {};
+template <class Epi>
+struct epi_slice_out<Epi, std::enable_if_t<Epi::kSliceOut>> : std::true_type {};
+
+// Slice-out of a tile of TOK tokens x TN blocks of 32 channels by NT threads: block i goes through LDS (patch[channel][token],
+// two buffers at lds, write(i, patch) fills one), and what it adds is in flight before the first of them is written: loads
+// behind each block's barrier had made a tile wait for memory once per block.  Maps and windows of whole 8-token
+// pieces move 16 bytes at a time; others (ragged) pairs of tokens, a wavefront 128 consecutive tokens of one channel, because
+// 16-byte accesses off their alignment are slower than 2-byte ones (45 x 50 positions, 7000 tokens x 640 channels: 51 and 36 us).
+template <int TN, int TOK, int NT, class Epi, class Write>
+__device__ __forceinline__ void slice_out_rows(char* lds, const Epi& epi, int64_t m0, int64_t M, int n_first, int N, Write write) {
+  constexpr int LDP = TOK + 4, BUF = 32 * LDP * 4;
+  const int tid = threadIdx.x;
+  auto patch = [&](int i) { return reinterpret_cast<float*>(lds + (i & 1) * BUF); };
+  if (!epi.ragged()) {
+    constexpr int CH = NT / (TOK / 8), NU = 32 / CH;  // channels at a time, pieces of a block per thread
+    const int t8 = tid % (TOK / 8) * 8, c0 = tid / (TOK / 8);
+    const bool inside = m0 + t8 < M;
+    const int64_t at = epi.place(inside ? m0 + t8 : 0);
+    u32x4_t xr[TN][NU];
+    float bias[TN][NU];
+#pragma unroll
+    for (int i = 0; i < TN; ++i)
+#pragma unroll
+      for (int u = 0; u < NU; ++u) {
+        const int n = n_first + 32 * i + c0 + CH * u, nc = n < N ? n : 0;
+        xr[i][u] = *reinterpret_cast<const u32x4_t*>(epi.x + at + epi.channel(nc));
+        bias[i][u] = param_or(epi.bias, nc, 0.f);
+      }
+#pragma unroll
+    for (int i = 0; i < TN; ++i) {
+      write(i, patch(i));
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < NU; ++u) {
+        const int n = n_first + 32 * i + c0 + CH * u;
+        if (!inside || n >= N) continue;
+        const float* row = patch(i) + (c0 + CH * u) * LDP + t8;
+        const float4 lo = *reinterpret_cast<const float4*>(row), hi = *reinterpret_cast<const float4*>(row + 4);
+        const float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+        u32x4_t o;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const float r0 = __uint_as_float(xr[i][u][k] << 16) + (v[2 * k] + bias[i][u]);
+          const float r1 = __uint_as_float(xr[i][u][k] & 0xffff0000u) + (v[2 * k + 1] + bias[i][u]);
+          o[k] = (unsigned)float_to_bf16_bits(r0) | ((unsigned)float_to_bf16_bits(r1) << 16);
+        }
+        *reinterpret_cast<u32x4_t*>(epi.out + at + epi.channel(n)) = o;
+      }
+    }
+  } else {
+    constexpr int PER = TOK / 128, CH = NT / kWave / PER;
+    const int wave = tid / kWave, tok = wave % PER * 128 + tid % kWave * 2, c0 = wave / PER;
+    const int64_t left = M - m0 - tok;
+    const int64_t a0 = epi.place(left > 0 ? m0 + tok : 0), a1 = epi.place(left > 1 ? m0 + tok + 1 : 0);
+    const bool joined = left > 1 && a1 == a0 + 1;  // neighbours
+#pragma unroll
+    for (int i = 0; i < TN; ++i) {
+      write(i, patch(i));
+      __syncthreads();
+      const int n1 = n_first + 32 * (i + 1) < N ? 32 : N - n_first - 32 * i;
+#pragma unroll 4
+      for (int ch = c0; ch < n1; ch += CH) {  // a short loop: unrolled over the blocks as well, its code takes longer to arrive than to run
+        const int n = n_first + 32 * i + ch;
+        const float2 v = *reinterpret_cast<const float2*>(patch(i) + ch * LDP + tok);
+        const float bn = param_or(epi.bias, n, 0.f);
+        const int64_t o0 = a0 + epi.channel(n), o1 = a1 + epi.channel(n);
+        if (joined && (o0 & 1) == 0) {
+          const unsigned xw = *reinterpret_cast<const unsigned*>(epi.x + o0);
+          const float r0 = __uint_as_float(xw << 16) + (v.x + bn), r1 = __uint_as_float(xw & 0xffff0000u) + (v.y + bn);
+          *reinterpret_cast<unsigned*>(epi.out + o0) = (unsigned)float_to_bf16_bits(r0) | ((unsigned)float_to_bf16_bits(r1) << 16);
+        } else {
+          if (left > 0) epi.out[o0] = from_float<bf16>(to_float(epi.x[o0]) + (v.x + bn));
+          if (left > 1) epi.out[o1] = from_float<bf16>(to_float(epi.x[o1]) + (v.y + bn));
+        }
+      }
+    }
+  }
+}
+
 template <int TM, int TN, int STAGES, bool F16, class Epi, bool WS = false>
 __global__ __launch_bounds__(WS ? 512 : 256, (WS && TM * TN > 2) ? 1 : 2) void ring_mma_kernel(ConvArgs a, Epi epi) {
   constexpr int AF = 4 * TM * 2, WFR = 2 * TN;           // fragments per stage
@@ -273,7 +359,18 @@ __global__ __launch_bounds__(WS ? 512 : 256, (WS && TM * TN > 2) ? 1 : 2) void r
   }
   __builtin_amdgcn_s_waitcnt(0x0070 | 0xF00);  // vmcnt(0): the padding loads of the last stages
 
-  if constexpr (Epi::kRows8) {
+  if constexpr (epi_slice_out<Epi>::value) {
+    static_assert(2 * 32 * (128 * TM + 4) * 4 <= STAGES * SLOT, "buffers fit the ring");
+    __syncthreads();  // the ring is no longer read
+    slice_out_rows<TN, 128 * TM, WS ? 512 : 256>(ring, epi, m0, a.M, col * TN * 32, a.O, [&](int i, float* patch) {
+      if (producer) return;
+#pragma unroll
+      for (int j = 0; j < TM; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) patch[(e / 4 * 8 + half * 4 + e % 4) * (128 * TM + 4) + (wave * TM + j) * 32 + trow] = acc[i][j][e];
+    });
+    return;
+  } else if constexpr (Epi::kRows8) {
     // Output channels are far apart in the feature, tokens adjacent: hand the epilogue 8 consecutive
     // tokens of one channel.  One 32-channel block at a time is transposed through the (now idle)
     // ring: patch[channel][token], rows padded by 4 floats.
@@ -330,6 +427,28 @@ __global__ __launch_bounds__(WS ? 512 : 256, (WS && TM * TN > 2) ? 1 : 2) void r
   for (int j = 0; j < TM; ++j) {
     const int64_t m = tok[j];
     if (m >= a.M) continue;
+    if constexpr (epi_residual<Epi>::value) {
+      // what the lane's 4 TN pieces of the residual stream hold, and their biases, in flight together (an N = K = 1280 projection of 2048
+      // tokens waited for memory 12 times behind its contraction)
+      float4 hv[4 * TN];
+      uint2 bv[4 * TN];
+      auto first = [&](int k) {
+        const int n = (col * TN + k / 4) * 32 + k % 4 * 8 + half * 4;
+        return n < a.O ? n : 0;
+      };
+#pragma unroll
+      for (int k = 0; k < 4 * TN; ++k) bv[k] = epi.bias ? *reinterpret_cast<const uint2*>(epi.bias + first(k)) : make_uint2(0u, 0u);
+#pragma unroll
+      for (int k = 0; k < 4 * TN; ++k)
+        hv[k] = epi.accumulate ? *reinterpret_cast<const float4*>(epi.h + m * epi.ld + first(k)) : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+      for (int k = 0; k < 4 * TN; ++k) {
+        const int n = (col * TN + k / 4) * 32 + k % 4 * 8 + half * 4;
+        const float v[4] = {acc[k / 4][j][k % 4 * 4 + 0], acc[k / 4][j][k % 4 * 4 + 1], acc[k / 4][j][k % 4 * 4 + 2], acc[k / 4][j][k % 4 * 4 + 3]};
+        if (n < a.O) epi.finish(m, n, v, hv[k], bv[k]);
+      }
+      continue;
+    }
 #pragma unroll
     for (int i = 0; i < TN; ++i) {
 #pragma unroll
@@ -391,11 +510,19 @@ struct EpiConvEmbFrag {
 // 16-byte accesses when the eight tokens are eight aligned positions of one image.
 struct EpiSliceOutRows {
   static constexpr bool kRows8 = true;
+  static constexpr bool kSliceOut = true;
   static constexpr bool kUp = false;
   const bf16* x;
   bf16* out;
   const bf16* bias;
   Window w;
+  // rows8 in two halves (slice_out_rows).  !ragged(): eight tokens are always aligned positions of one image.
+  __device__ __forceinline__ bool ragged() const { return ((w.P | w.p0 | w.Pw) & 7) != 0; }
+  __device__ __forceinline__ int64_t place(int64_t m) const {  // of token m, channel 0
+    const int mi = (int)m, bf = mi / w.Pw;
+    return ((int64_t)(bf / w.Fw) * w.C * w.F + (w.f0 + bf % w.Fw)) * w.P + w.p0 + mi % w.Pw;
+  }
+  __device__ __forceinline__ int64_t channel(int n) const { return (int64_t)n * w.F * w.P; }
   __device__ __forceinline__ void operator()(int64_t, int, const float (&)[4]) const {}
   __device__ __forceinline__ void rows8(int64_t m, int n, const float (&v)[8], int64_t M) const {
     const float bn = param_or(bias, n, 0.f);
@@ -502,16 +629,25 @@ __global__ __launch_bounds__(256) void pack_conv_kernel(const bf16* __restrict__
 
 // e[b, o] = b_t[o] + sum_k SiLU(temb[b, k]) * W_t[k, o].  One block (16 wavefronts) per (64 outputs,
 // batch entry): wavefront q sums k = q, q+16, ... for output o = lane; the 16 partial sums are added
-// in a fixed order.
+// in a fixed order.  The activations are formed once, in LDS, so that nothing but independent loads is left in the sum.
+constexpr int kTembChunk = 4096;  // a multiple of 16
 __global__ __launch_bounds__(1024) void temb_proj_kernel(const bf16* __restrict__ temb, const bf16* __restrict__ wt,
                                                          const bf16* __restrict__ bt, float* __restrict__ e, int Kt, int O) {
   const int lane = threadIdx.x % kWave, q = threadIdx.x / kWave;
   const int o = blockIdx.x * kWave + lane;
   const int b = blockIdx.y;
+  __shared__ float act[kTembChunk];
   float s = 0.f;
-  if (o < O) {
-#pragma unroll 8
-    for (int k = q; k < Kt; k += 16) s = fmaf(silu(to_float(temb[(int64_t)b * Kt + k])), to_float(wt[(int64_t)k * O + o]), s);
+  for (int k0 = 0; k0 < Kt; k0 += kTembChunk) {
+    const int n = Kt - k0 < kTembChunk ? Kt - k0 : kTembChunk;
+    __syncthreads();
+    for (int k = threadIdx.x; k < n; k += 1024) act[k] = silu(to_float(temb[(int64_t)b * Kt + k0 + k]));
+    __syncthreads();
+    if (o < O) {
+      const bf16* w = wt + (int64_t)k0 * O + o;
+#pragma unroll 16
+      for (int k = q; k < n; k += 16) s = fmaf(act[k], to_float(w[(int64_t)k * O]), s);
+    }
   }
   __shared__ float part[16][kWave];
   part[q][lane] = s;
@@ -740,38 +876,37 @@ __global__ __launch_bounds__(256) void window_to_tokens_silu_kernel(const bf16* 
   const int b = bf / w.Fw, fl = bf % w.Fw, f = w.f0 + fl;
   const int pt = blockIdx.x * 64, ct = blockIdx.y * 64;
   const int ng = w.C / w.G;
-  const bool vec_ok = (w.P % 4 == 0) && (w.p0 % 4 == 0);
+  if (pt + 64 <= w.Pw && ct + 64 <= w.C) {
+    const SliceTile t = load_slice_tile<bf16>(x, RAW ? nullptr : stats, RAW ? nullptr : gamma, RAW ? nullptr : beta, w, b, f, pt, ct, ng);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int id = threadIdx.x + i * 256, cl = id / 16, pq = (id % 16) * 4;
-    const int c = ct + cl, pl = pt + pq;
-    float v[4] = {0.f, 0.f, 0.f, 0.f};
-    if (c < w.C && pl < w.Pw) {
-      float mean = 0.f, ga = 1.f, be = 0.f;
-      if constexpr (!RAW) {
-        const int g = c / ng;
-        mean = stats[(((int64_t)b * w.F + f) * w.G + g) * 2 + 0];
-        ga = param_or(gamma, c, 1.f) * stats[(((int64_t)b * w.F + f) * w.G + g) * 2 + 1];
-        be = param_or(beta, c, 0.f);
-      }
-      const bf16* src = x + (((int64_t)b * w.C + c) * w.F + f) * w.P + w.p0 + pl;
-      float xv[4] = {0.f, 0.f, 0.f, 0.f};
-      if (vec_ok && pl + 3 < w.Pw) {
-        const uint2 raw = *reinterpret_cast<const uint2*>(src);
-        xv[0] = __uint_as_float(raw.x << 16);
-        xv[1] = __uint_as_float(raw.x & 0xffff0000u);
-        xv[2] = __uint_as_float(raw.y << 16);
-        xv[3] = __uint_as_float(raw.y & 0xffff0000u);
-      } else {
+    for (int i = 0; i < 4; ++i) {
+      const float ga = t.ga[i] * t.rstd[i];
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        tile[threadIdx.x / 16 + 16 * i][threadIdx.x % 16 * 4 + j] = RAW ? t.x(i, j) : silu((t.x(i, j) - t.mean[i]) * ga + t.be[i]);
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int id = threadIdx.x + i * 256, cl = id / 16, pq = (id % 16) * 4;
+      const int c = ct + cl, pl = pt + pq;
+      float v[4] = {0.f, 0.f, 0.f, 0.f};
+      if (c < w.C && pl < w.Pw) {
+        float mean = 0.f, ga = 1.f, be = 0.f;
+        if constexpr (!RAW) {
+          const int g = c / ng;
+          mean = stats[(((int64_t)b * w.F + f) * w.G + g) * 2 + 0];
+          ga = param_or(gamma, c, 1.f) * stats[(((int64_t)b * w.F + f) * w.G + g) * 2 + 1];
+          be = param_or(beta, c, 0.f);
+        }
+        const bf16* src = x + (((int64_t)b * w.C + c) * w.F + f) * w.P + w.p0 + pl;
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-          if (pl + j < w.Pw) xv[j] = to_float(src[j]);
+          if (pl + j < w.Pw) v[j] = RAW ? to_float(src[j]) : silu((to_float(src[j]) - mean) * ga + be);
       }
 #pragma unroll
-      for (int j = 0; j < 4; ++j) v[j] = RAW ? xv[j] : silu((xv[j] - mean) * ga + be);
+      for (int j = 0; j < 4; ++j) tile[cl][pq + j] = v[j];
     }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) tile[cl][pq + j] = v[j];
   }
   __syncthreads();
 #pragma unroll

@@ -11,8 +11,9 @@
 // per wavefront and every other step, because a load blocks its wavefront while the address unit takes it: all at once
 // behind the barrier they made the first of the calls below 2262 us instead of 2152, and with 4 wavefronts of 96 x 160,
 // where they stop the only wavefront of a SIMD, it took 2697.
-// One frame of 72 x 128 x 2, 320 channels, alone on the GPU: 50 us, of which the MFMAs of the 144 workgroups' 90 taps (640
-// cycles each) are 24; prologue, exchange and epilogue are outside the taps.
+// In the kernel, cycles, one frame of 72 x 128 x 2, 320 channels (144 workgroups): 700 per tap, 660 of them the MFMAs of a SIMD's two
+// wavefronts, x 90; prologue 5.4 k, exchange 4 k, epilogue 12 k (conv1) and 10.5 k (conv2, whose slice-out waited for x once per
+// channel block before: 52.6 -> 50.3 us per launch).  At 1.8 GHz, which MFMAs on such data leave, that is the 50 us.
 // Measured (ring kernel -> this one): ResBlock of 320 channels on 72 x 128, 25 frames one at a time, 2450 -> 2240 us; 640
 // channels on 36 x 64, 16 frames two at a time, 1490 -> 1267 us; 640 channels doubled to 72 x 128, 12 frames, 1630 ->
 // 1394 us (1.0 -> 1.17 PFLOP/s).
@@ -123,9 +124,9 @@ __global__ __launch_bounds__(512, 2) void conv_halo_kernel(ConvArgs a, int nblk,
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
-  // Fragments: a weight fragment serves the TM MFMAs of one step and is read two steps ahead; the next tap's
-  // activations are read in the last two steps of a tap.
-  u32x4_t wf[3], af[2][TM];
+  // Fragments: a weight fragment serves the TM MFMAs of one step and is read three steps ahead, the next tap's activations two
+  // or three.
+  u32x4_t wf[TN], af[2][TM];
   auto read_w = [&](int cc, int r, int t, int i) {
     return *reinterpret_cast<const u32x4_t*>(lds + ((cc + r) & 1) * WST + (t * WFR + ks * TN + i) * 1024 + lane * 16);
   };
@@ -162,10 +163,11 @@ __global__ __launch_bounds__(512, 2) void conv_halo_kernel(ConvArgs a, int nblk,
     for (int i = 0; i < NLA; ++i) load_a(0, p, i, 0);
   stage_barrier(All());
   refill(-1, 2, 0);
+  refill(-1, 2, 1);
 #pragma unroll
   for (int j = 0; j < TM; ++j) af[0][j] = read_a(0, 0, 0, j);
-  wf[0] = read_w(0, 0, 0, 0);
-  wf[1] = read_w(0, 0, 0, 1);
+#pragma unroll
+  for (int i = 0; i < TN - 2; ++i) wf[i] = read_w(0, 0, 0, i);
   static_assert(TN == 5 && TM == 2, "step order");
   for (int cc = 0; cc < nch; ++cc) {
     // opaque: the taps' offsets and masks are not to be kept in registers across chunks
@@ -178,24 +180,21 @@ __global__ __launch_bounds__(512, 2) void conv_halo_kernel(ConvArgs a, int nblk,
       const int ntap = (tap + 1) % 9, ncc = tap == 8 ? cc + 1 : cc;
 #pragma unroll
       for (int i = 0; i < TN; ++i) {
-        const int step = tap * TN + i;
         // Nobody reads this stage any more (its last fragments are in registers) and the next one's data has had time
         // to land; the part of a patch that came with it is not needed before the next chunk.
-        if (t == 2 && i == 3) {
+        if (t == 2 && i == 2) {
           if (r == 2) stage_barrier(All());
           else stage_barrier(NotPatch());
         }
-        if (i < 3) wf[(step + 2) % 3] = read_w(cc, r, t, i + 2);
-        else {
-          wf[(step + 2) % 3] = read_w(ncc, ntap / 3, ntap % 3, i - 3);
-          af[(tap + 1) & 1][i - 3] = read_a(ncc, ntap / 3, ntap % 3, i - 3);
-        }
+        if (i < 2) wf[i + 3] = read_w(cc, r, t, i + 3);
+        else wf[i - 2] = read_w(ncc, ntap / 3, ntap % 3, i - 2);
+        if (i == 2 || i == 3) af[(tap + 1) & 1][i - 2] = read_a(ncc, ntap / 3, ntap % 3, i - 2);
 #pragma unroll
-        for (int j = 0; j < TM; ++j) mma(wf[step % 3], af[tap & 1][j], acc[i][j]);
+        for (int j = 0; j < TM; ++j) mma(wf[i], af[tap & 1][j], acc[i][j]);
         // the loads of a refill, one every other step from the barrier on
-        const int since = t == 2 ? i - 3 : t * TN + i + 2;  // steps behind the barrier
+        const int since = t == 2 ? i - 2 : t * TN + i + 3;  // steps behind the barrier
         __builtin_amdgcn_sched_barrier(0);
-        if (t == 2 && i == 3) refill(cc, r, 0);
+        if (t == 2 && since >= 0 && since % 2 == 0) refill(cc, r, since / 2);
         else if (t < 2 && since % 2 == 0 && since / 2 < NL) refill(r == 0 ? cc - 1 : cc, r == 0 ? 2 : r - 1, since / 2);
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -239,7 +238,14 @@ __global__ __launch_bounds__(512, 2) void conv_halo_kernel(ConvArgs a, int nblk,
   }
 
   const int trel = pair * 64 + ks * 32 + trow;  // the lane's token of the tile
-  if constexpr (Epi::kRows8) {  // 8 consecutive tokens of one channel at a time, transposed through LDS
+  if constexpr (epi_slice_out<Epi>::value) {
+    static_assert(2 * 32 * (kHaloTokens + 4) * 4 <= ZERO, "buffers fit");
+    __syncthreads();  // the exchange has been read
+    slice_out_rows<TN, kHaloTokens, 512>(lds, epi, m0, M, col * TN * 32, a.O, [&](int i, float* patch) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) patch[(e / 4 * 8 + half * 4 + e % 4) * (kHaloTokens + 4) + trel] = acc[i][0][e];
+    });
+  } else if constexpr (Epi::kRows8) {  // 8 consecutive tokens of one channel at a time, transposed through LDS
     constexpr int TOK = 256, LDP = TOK + 4;
     static_assert(32 * LDP * 4 <= ZERO, "patch fits");
     float* patch = reinterpret_cast<float*>(lds);

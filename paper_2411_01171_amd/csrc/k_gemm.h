@@ -126,6 +126,15 @@ struct EpiResidual {
       for (int i = 0; i < 4; ++i) c[i] = from_float<T>(ov[i]);
     }
   }
+  // The same from values read ahead: o of the residual stream, b four 16-bit biases
+  __device__ __forceinline__ void finish(int64_t m, int n0, const float (&v)[4], float4 o, uint2 b) const {
+    o.x += v[0] + __uint_as_float(b.x << 16);
+    o.y += v[1] + __uint_as_float(b.x & 0xffff0000u);
+    o.z += v[2] + __uint_as_float(b.y << 16);
+    o.w += v[3] + __uint_as_float(b.y & 0xffff0000u);
+    *reinterpret_cast<float4*>(h + m * ld + n0) = o;
+    if (copy) store_copy(m, n0, o);
+  }
   __device__ __forceinline__ void operator()(int64_t m, int n0, const float (&v)[4]) const {
     float4* p = reinterpret_cast<float4*>(h + m * ld + n0);
     float4 o = accumulate ? *p : make_float4(0.f, 0.f, 0.f, 0.f);

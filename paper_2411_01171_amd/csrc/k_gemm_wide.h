@@ -17,11 +17,6 @@
 
 namespace si {
 
-template <class Epi, class = void>
-struct epi_residual : std::false_type {};
-template <class Epi>
-struct epi_residual<Epi, std::enable_if_t<Epi::kResidual>> : std::true_type {};
-
 // a.act, a.wf, a.M, a.C (contraction length, a multiple of 64), a.O as in ring_mma_kernel, the weights packed in column tiles of
 // 160; a.ncol: column tiles of this kernel; a.ntiles, a.col_major likewise.
 template <int WC, int TM, int NSLOT, bool F16, class Epi>
@@ -162,33 +157,16 @@ __global__ __launch_bounds__(256 * WC, WC == 2 ? 2 : 1) void gemm_160_kernel(Con
 #pragma unroll
       for (int i = 0; i < TN; ++i) epi.block32(m, m < a.M, column(i), acc[i][j], half, ahead[i]);
     }
-  } else if constexpr (Epi::kRows8) {
-    // 8 consecutive tokens of one channel at a time, transposed through the idle slots: a 32-column block per step, in two
-    // buffers, so that a step's reads and stores run beside the next one's writes
-    static_assert(WC == 1, "one column tile");
-    constexpr int LDP = TOK + 4, BUF = 32 * LDP * 4;
-    static_assert(2 * BUF <= NSLOT * SLOT, "buffers fit");
+  } else if constexpr (epi_slice_out<Epi>::value) {
+    static_assert(WC == 1 && 2 * 32 * (TOK + 4) * 4 <= NSLOT * SLOT, "one column tile, buffers fit");
     __builtin_amdgcn_s_waitcnt(0x0070 | 0xF00);  // vmcnt(0): the padding loads of the last stages
     __syncthreads();
-#pragma unroll
-    for (int i = 0; i < TN; ++i) {
-      float* patch = reinterpret_cast<float*>(lds + (i & 1) * BUF);
+    slice_out_rows<TN, TOK, 256>(lds, epi, m0, a.M, column(0), a.O, [&](int i, float* patch) {
 #pragma unroll
       for (int j = 0; j < TM; ++j)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) patch[(e / 4 * 8 + half * 4 + e % 4) * LDP + (wrow * TM + j) * 32 + trow] = acc[i][j][e];
-      __syncthreads();
-#pragma unroll
-      for (int u = 0; u < 2 * TM; ++u) {
-        const int id = tid + u * 256, ch = id / (TOK / 8), t8 = (id % (TOK / 8)) * 8;
-        if (m0 + t8 < a.M) {
-          const float4 lo = *reinterpret_cast<const float4*>(patch + ch * LDP + t8);
-          const float4 hi = *reinterpret_cast<const float4*>(patch + ch * LDP + t8 + 4);
-          const float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-          epi.rows8(m0 + t8, column(i) + ch, v, a.M);
-        }
-      }
-    }
+        for (int e = 0; e < 16; ++e) patch[(e / 4 * 8 + half * 4 + e % 4) * (TOK + 4) + (wrow * TM + j) * 32 + trow] = acc[i][j][e];
+    });
   } else if constexpr (epi_residual<Epi>::value) {
     // Rows of the fp32 residual stream through the idle slots: a result lane holds four columns of one token, and going to
     // memory like that, 32 rows per instruction, took 16.5 k cycles of a tile (as much as its contraction over 1280 channels),
@@ -248,6 +226,7 @@ __global__ __launch_bounds__(256 * WC, WC == 2 ? 2 : 1) void gemm_160_kernel(Con
       if (u / G < rows) *reinterpret_cast<float4*>(base + offset(u)) = reinterpret_cast<const float4*>(lds)[u];
     }
   } else {
+    static_assert(!Epi::kRows8, "no such epilogue");
     __builtin_amdgcn_s_waitcnt(0x0070 | 0xF00);
 #pragma unroll
     for (int j = 0; j < TM; ++j) {
