@@ -506,17 +506,17 @@ struct EpiConvEmbFrag {
 };
 
 // Slice-out of the ResBlock: out[b, n, f, p] = x[b, n, f, p] + acc + bias[n] for 8 consecutive tokens
-// m .. m+7 of the window (token = (b*Fw + f - f0)*Pw + p); the sum is formed in fp32 and rounded once.
-// 16-byte accesses when the eight tokens are eight aligned positions of one image.
+// m .. m+7 of the window (token = (b*Fw + f - f0)*Pw + p); the sum is formed in fp32 and rounded once
+// (slice_out_rows, which every kernel with this epilogue ends in).
 struct EpiSliceOutRows {
-  static constexpr bool kRows8 = true;
+  static constexpr bool kRows8 = false;
   static constexpr bool kSliceOut = true;
   static constexpr bool kUp = false;
   const bf16* x;
   bf16* out;
   const bf16* bias;
   Window w;
-  // rows8 in two halves (slice_out_rows).  !ragged(): eight tokens are always aligned positions of one image.
+  // What slice_out_rows asks.  !ragged(): eight tokens are always aligned positions of one image.
   __device__ __forceinline__ bool ragged() const { return ((w.P | w.p0 | w.Pw) & 7) != 0; }
   __device__ __forceinline__ int64_t place(int64_t m) const {  // of token m, channel 0
     const int mi = (int)m, bf = mi / w.Pw;
@@ -524,35 +524,6 @@ struct EpiSliceOutRows {
   }
   __device__ __forceinline__ int64_t channel(int n) const { return (int64_t)n * w.F * w.P; }
   __device__ __forceinline__ void operator()(int64_t, int, const float (&)[4]) const {}
-  __device__ __forceinline__ void rows8(int64_t m, int n, const float (&v)[8], int64_t M) const {
-    const float bn = param_or(bias, n, 0.f);
-    const int mi = (int)m;  // window tokens fit 31 bits: 32-bit divisions
-    const int pl = mi % w.Pw;
-    const int64_t bf = mi / w.Pw;
-    const int64_t off = ((((int64_t)((int)bf / w.Fw)) * w.C + n) * w.F + (w.f0 + (int)bf % w.Fw)) * w.P + w.p0 + pl;
-    if (pl + 7 < w.Pw && m + 7 < M && ((w.P | w.p0 | pl) & 7) == 0) {
-      const uint4 raw = *reinterpret_cast<const uint4*>(x + off);
-      const unsigned xw[4] = {raw.x, raw.y, raw.z, raw.w};
-      unsigned ow[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float r0 = __uint_as_float(xw[i] << 16) + (v[2 * i] + bn);
-        const float r1 = __uint_as_float(xw[i] & 0xffff0000u) + (v[2 * i + 1] + bn);
-        ow[i] = (unsigned)float_to_bf16_bits(r0) | ((unsigned)float_to_bf16_bits(r1) << 16);
-      }
-      *reinterpret_cast<uint4*>(out + off) = make_uint4(ow[0], ow[1], ow[2], ow[3]);
-    } else {
-#pragma unroll
-      for (int t = 0; t < 8; ++t) {
-        const int64_t mt = m + t;
-        if (mt >= M) break;
-        const int plt = (int)mt % w.Pw;
-        const int64_t bft = (int)mt / w.Pw;
-        const int64_t o2 = ((((int64_t)((int)bft / w.Fw)) * w.C + n) * w.F + (w.f0 + (int)bft % w.Fw)) * w.P + w.p0 + plt;
-        out[o2] = from_float<bf16>(to_float(x[o2]) + (v[t] + bn));
-      }
-    }
-  }
 };
 
 // out[b, n, f, p] = acc + bias[n] for 8 consecutive tokens of the window (no residual): the

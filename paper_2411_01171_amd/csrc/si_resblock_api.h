@@ -98,8 +98,8 @@ static void launch_conv_tile(const ConvArgs& a, Epi epi, hipStream_t st) {
 // Column tiles of the convolution kernel: the candidate width that pads the output channels least,
 // the wider one on a tie.  rows_in_flight = 128-token row tiles of the windows in flight: while the
 // launches together leave CUs without a workgroup, a narrower tile (4 or 2 blocks of 32 channels,
-// never one: measured slower throughout) that pads at most a tenth more takes its place (down-
-// sampling of a 72 x 128 map at 320 channels: 2 x 72 workgroups of 160 channels -> 2 x 180 of 64).
+// never one: measured slower throughout) that pads at most a tenth more takes its place (320
+// channels over 72 row tiles: 2 x 72 workgroups of 160 channels -> 5 x 72 of 64).
 static void conv_column_tiles(int O, int64_t rows_in_flight, int* TN, int* ncol) {
   *TN = 1;
   *ncol = (O + 31) / 32;
