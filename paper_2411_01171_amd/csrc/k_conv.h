@@ -40,7 +40,8 @@ __device__ __forceinline__ float silu(float v) { return v / (1.f + __expf(-v)); 
 //               are (32-token block, 16-channel step) pairs, 16-channel steps fastest.  The buffer starts
 //               with a 256-byte block of zeros (what a tap outside the image reads).
 //   weights     per (column tile, k-tile of 32 input channels of one tap): 2 k-steps x TN fragments,
-//               rows = output channels; k-tiles ordered tap-major (tap = 3*(dy+1) + dx+1).
+//               rows = output channels; k-tiles ordered tap-major (tap = 3*(dy+1) + dx+1).  CHUNKS: k-steps of 16 input
+//               channels, ordered channel-major with the nine taps inside.
 
 enum ConvMode { kConvSame = 0, kConvStride2 = 1, kConvNearestUp = 2 };
 
@@ -79,6 +80,9 @@ struct ConvArgs {
 // latency then overlap with the MFMAs instead of preceding them, which is what a launch with one
 // workgroup per CU at most lacks.  Both roles pass the same barriers: one per k-tile, then those of
 // the epilogue.
+// CHUNKS (stride 2 only): the contraction runs over chunks of 16 input channels with the nine taps inside, conv_down_kernel's
+// order, instead of over taps with the channels inside.  Sums, and so the results' bits, are that kernel's; a call may take
+// either for its windows.
 template <class Epi, class = void>
 struct epi_block32 : std::false_type {};
 template <class Epi>
@@ -170,7 +174,7 @@ __device__ __forceinline__ void slice_out_rows(char* lds, const Epi& epi, int64_
   }
 }
 
-template <int TM, int TN, int STAGES, bool F16, class Epi, bool WS = false>
+template <int TM, int TN, int STAGES, bool F16, class Epi, bool WS = false, bool CHUNKS = false>
 __global__ __launch_bounds__(WS ? 512 : 256, (WS && TM * TN > 2) ? 1 : 2) void ring_mma_kernel(ConvArgs a, Epi epi) {
   constexpr int AF = 4 * TM * 2, WFR = 2 * TN;           // fragments per stage
   constexpr int NW = (WFR + 3) / 4;                      // weight loads per wavefront per stage
@@ -241,7 +245,41 @@ __global__ __launch_bounds__(WS ? 512 : 256, (WS && TM * TN > 2) ? 1 : 2) void r
     }
   };
   int ld_tap = 0, ld_c = 0, ld_kt = 0;  // the k-tile the next issue() loads
-  set_tap(0);
+  // CHUNKS: where the loads of the next k-tile's two k-steps go; aim() forms it while the LDS reads before it are under way
+  // (between the barrier and the loads, its instructions took 1.3 .. 1.7 times the launch's time)
+  const int nchunk = a.C / 16;
+  int centre[TM], inside[TM];  // source token at the centre tap; bit t: tap t lies inside the map
+  int step_tap = 0, step_shift = -a.Wi - 1, step_c = 0;  // the next k-step: tap, its shift, chunk
+  unsigned aim_act[TM][2];
+  auto aim = [&]() {
+    const int real = ld_kt < nkt;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      const int last = step_tap >> 3, row_end = 0x24 >> step_tap & 1;  // tap 8; taps 2 and 5
+#pragma unroll
+      for (int j = 0; j < TM; ++j) {
+        const unsigned src = (unsigned)(centre[j] + step_shift);
+        unsigned at = (unsigned)kActZeroBytes + (unsigned)half * 512u + (src & 31) * 16u + (((src >> 5) * (unsigned)nchunk + (unsigned)step_c) << 10);
+        asm("" : "+v"(at));  // a select, no branch
+        aim_act[j][ks] = inside[j] & (real << step_tap) ? at : (unsigned)(lane * 16 % kActZeroBytes);
+        asm volatile("" : "+v"(aim_act[j][ks]));
+      }
+      step_shift += 1 + row_end * (a.Wi - 3) - last * (2 * a.Wi + 3);
+      step_c += last;
+      step_tap += 1 - 9 * last;
+    }
+  };
+  if constexpr (CHUNKS) {
+#pragma unroll
+    for (int j = 0; j < TM; ++j) {
+      centre[j] = (int)img0[j] + 2 * py[j] * a.Wi + 2 * px[j];
+      inside[j] = 0;
+#pragma unroll
+      for (int t = 0; t < 9; ++t)
+        if ((unsigned)(2 * py[j] + t / 3 - 1) < (unsigned)a.Hi && (unsigned)(2 * px[j] + t % 3 - 1) < (unsigned)a.Wi) inside[j] |= 1 << t;
+    }
+    aim();
+  } else set_tap(0);
   auto issue = [&]() {
     const unsigned slot = ring_lds + (unsigned)((ld_kt % STAGES) * SLOT);
     const bool real = ld_kt < nkt;
@@ -249,7 +287,9 @@ __global__ __launch_bounds__(WS ? 512 : 256, (WS && TM * TN > 2) ? 1 : 2) void r
     for (int j = 0; j < TM; ++j)
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) {
-        const unsigned voff = (real && tapv[j]) ? tapv[j] + (unsigned)((ld_c * 2 + ks) * 1024) : (unsigned)(lane * 16 % kActZeroBytes);
+        unsigned voff;
+        if constexpr (CHUNKS) voff = aim_act[j][ks];
+        else voff = (real && tapv[j]) ? tapv[j] + (unsigned)((ld_c * 2 + ks) * 1024) : (unsigned)(lane * 16 % kActZeroBytes);
         const unsigned dst = slot + (unsigned)((((wave * TM + j) * 2 + ks)) * 1024);
         asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(voff), "s"(a.act), "s"(dst) : "memory");
       }
@@ -263,6 +303,7 @@ __global__ __launch_bounds__(WS ? 512 : 256, (WS && TM * TN > 2) ? 1 : 2) void r
       asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(voff), "s"(sb), "s"(dst) : "memory");
     }
     ++ld_kt;
+    if constexpr (CHUNKS) return;
     if (++ld_c == per_tap) {
       ld_c = 0;
       if (++ld_tap < a.ntaps) set_tap(ld_tap);
@@ -312,11 +353,15 @@ __global__ __launch_bounds__(WS ? 512 : 256, (WS && TM * TN > 2) ? 1 : 2) void r
   if constexpr (WS) {
     if (producer) {
 #pragma unroll
-      for (int s = 0; s < STAGES - 1; ++s) issue();
+      for (int s = 0; s < STAGES - 1; ++s) {
+        issue();
+        if constexpr (CHUNKS) aim();
+      }
       for (int kt = 0; kt < nkt; ++kt) {
         __builtin_amdgcn_s_waitcnt(kWaitImm);  // this wavefront's share of k-tile kt has landed
         __syncthreads();                       // barrier kt: every share has; k-tile kt-1's slot is no longer read
         issue();
+        if constexpr (CHUNKS) aim();
       }
     } else {
       // barrier kt opens k-tile kt; its fragments are in registers (lgkmcnt(0)) before barrier kt+1 lets
@@ -346,7 +391,10 @@ __global__ __launch_bounds__(WS ? 512 : 256, (WS && TM * TN > 2) ? 1 : 2) void r
     }
   } else {
 #pragma unroll
-    for (int s = 0; s < STAGES - 1; ++s) issue();
+    for (int s = 0; s < STAGES - 1; ++s) {
+      issue();
+      if constexpr (CHUNKS) aim();
+    }
     for (int kt = 0; kt < nkt; ++kt) {
       // k-tile kt has landed for this wavefront once at most the STAGES-2 younger stages are in flight
       __builtin_amdgcn_s_waitcnt(kWaitImm);
@@ -354,6 +402,7 @@ __global__ __launch_bounds__(WS ? 512 : 256, (WS && TM * TN > 2) ? 1 : 2) void r
       issue();          // which the stage loaded now reuses
       Frags f;
       read_frags(kt, f);
+      if constexpr (CHUNKS) aim();
       contract(f);
     }
   }
@@ -564,7 +613,8 @@ struct EpiStoreRows {
 // element e of lane l of fragment ((col*nkt + kt)*2 + ks)*TN + i is w[o, c, tap] with
 // o = (col*TN + i)*32 + l%32, tap = kt / (C/32), c = (kt % (C/32))*32 + ks*16 + (l/32)*8 + e; rows
 // beyond O are zero.  One thread per element.  Block 0 also clears the operand buffers' zero blocks.
-template <bool F16>
+// CHUNKS: k-steps in ring_mma_kernel's CHUNKS order, tap = s % 9, c = s / 9 * 16 + (l/32)*8 + e for s = 2 kt + ks.
+template <bool F16, bool CHUNKS = false>
 __global__ __launch_bounds__(256) void pack_conv_kernel(const bf16* __restrict__ src, unsigned short* __restrict__ dst, int O, int C,
                                                         int TN, int ncol, unsigned* __restrict__ zero0, int zero_lanes = 0,
                                                         int64_t zero_lane_stride = 0, int64_t zero_pair = 0, int ntaps = 9) {
@@ -588,7 +638,8 @@ __global__ __launch_bounds__(256) void pack_conv_kernel(const bf16* __restrict__
   const int kt = (int)(f % nkt);
   const int col = (int)(f / nkt);
   const int o = (col * TN + i) * 32 + l % 32;
-  const int tap = kt / per_tap, c = (kt % per_tap) * 32 + ks * 16 + (l / 32) * 8 + e;
+  const int tap = CHUNKS ? (2 * kt + ks) % 9 : kt / per_tap;
+  const int c = (CHUNKS ? (2 * kt + ks) / 9 * 16 : (kt % per_tap) * 32 + ks * 16) + (l / 32) * 8 + e;
   unsigned short bits = 0;
   if (o < O) {
     const bf16 v = src[((int64_t)o * C + c) * ntaps + tap];

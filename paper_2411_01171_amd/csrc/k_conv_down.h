@@ -1,5 +1,6 @@
 // DownSample: 3x3 convolution of stride 2 that reads the feature as it lies in memory -- [image][channel][position], bf16 --
-// and therefore takes every window of a call in one launch: no operand buffer, no slice-in pass.
+// and therefore takes every window of a call in one launch: no operand buffer, no slice-in pass.  Calls of many windows or
+// of many full tiles run on it (down_pays, si_resblock_api.h), the others on the ring kernel, summing in the same order.
 //
 // What bounded the ring kernel (k_conv.h) here was delivery, every source token once per tap, and launches of 180
 // workgroups with a copy pass of 12 us before each.  A workgroup of 8 wavefronts owns 256 consecutive output positions of
@@ -24,7 +25,7 @@ struct ConvDownArgs {
   const bf16* src;   // element (image, c, p) at (image / F * C + c) * F * P + image % F * P + p
   bf16* out;         // the same of O channels, Po positions
   const bf16* bias;  // may be NULL
-  const char* wf;    // fragment-ordered kernel, column tiles of 320 channels (pack_conv_kernel)
+  const char* wf;    // fragment-ordered kernel, column tiles of 320 channels (pack_conv_kernel, CHUNKS)
   int C, O, F;       // input / output channels, frames per batch entry
   int W, H, P;       // source map
   int Wo, Po;        // output map
@@ -75,26 +76,21 @@ __global__ __launch_bounds__(512, 2) void conv_down_kernel(ConvDownArgs a) {
   // ---- weights: load i of this wavefront fetches fragment id = wave + 8 i of a stage's 30 (ids past them repeat the last)
   const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) void*)lds;
   constexpr int NLW = (3 * WFR + 7) / 8;
-  const char* wchunk = a.wf + (int64_t)col * (9 * nch) * (WFR * 1024);  // kernel row 0 of the current chunk
-  const unsigned wrow = (unsigned)(3 * nch) * (WFR * 1024);             // bytes from one kernel row to the next
-  unsigned wsrc[NLW], wdst[NLW];
+  const char* wchunk = a.wf + (int64_t)col * nch * (3 * WST);  // the current chunk's three stages
+  unsigned wsrc[NLW];
 #pragma unroll
-  for (int i = 0; i < NLW; ++i) {
-    const int id = wave + 8 * i < 3 * WFR ? wave + 8 * i : 3 * WFR - 1, t = id / WFR;
-    wsrc[i] = (unsigned)(t * nch * WFR + id - t * WFR) * 1024;
-    wdst[i] = lds0 + (unsigned)(id * 1024);
-  }
+  for (int i = 0; i < NLW; ++i) wsrc[i] = (unsigned)(wave + 8 * i < 3 * WFR ? wave + 8 * i : 3 * WFR - 1) * 1024;
   auto load_w = [&](const char* row, int i, int buf) {
     asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1"
                  :
-                 : "v"((unsigned)(lane * 16)), "s"(row + wsrc[i]), "s"(wdst[i] + (unsigned)(buf * WST))
+                 : "v"((unsigned)(lane * 16)), "s"(row + wsrc[i]), "s"(lds0 + wsrc[i] + (unsigned)(buf * WST))
                  : "memory");
   };
   // i-th load of what takes the place of stage (cc, r) when everybody has left it: the stage after the next.  Past the
   // last chunk the last one is fetched once more, into slots nobody reads.  wchunk is chunk wc's.
   auto refill = [&](int cc, int wc, int r, int i) {
     const int ahead = (r == 0 ? cc : cc + 1) - wc;
-    load_w(wchunk + (ahead && wc + 1 < nch ? WFR * 1024 : 0) + (r == 0 ? 2 : r - 1) * wrow, i, (cc + r) & 1);
+    load_w(wchunk + (ahead && wc + 1 < nch ? 3 * WST : 0) + (r == 0 ? 2 : r - 1) * WST, i, (cc + r) & 1);
   };
 
   // ---- patch: unit u of a thread is the chunk's channels 4 * quad .. + 3 at the positions of one group.
@@ -137,7 +133,7 @@ __global__ __launch_bounds__(512, 2) void conv_down_kernel(ConvDownArgs a) {
 #pragma unroll
   for (int i = 0; i < NLW; ++i) load_w(wchunk, i, 0);
 #pragma unroll
-  for (int i = 0; i < 1; ++i) load_w(wchunk + wrow, i, 1);
+  for (int i = 0; i < 1; ++i) load_w(wchunk + WST, i, 1);
   if (tid < 4) *reinterpret_cast<unsigned*>(lds + ZERO + 4 * tid) = 0u;
   // per row tile: the lane's source granule at the centre tap; bit t of the mask: tap t lies inside the image
   int base[TM], mask[TM];
@@ -252,7 +248,7 @@ __global__ __launch_bounds__(512, 2) void conv_down_kernel(ConvDownArgs a) {
       }
 #pragma unroll
       for (int j = 0; j < TM; ++j) af[0][j] = af[1][j];
-      if (cc + 1 < nch) wchunk += WFR * 1024;
+      if (cc + 1 < nch) wchunk += 3 * WST;
     }
     __builtin_amdgcn_s_setprio(0);
   };

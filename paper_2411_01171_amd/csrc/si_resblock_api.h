@@ -89,10 +89,13 @@ static si_status make_res_plan(const si_tensor5* x, const si_resblock_weights* w
   return SI_OK;
 }
 
-template <int TM, int TN, int STAGES, bool F16, class Epi>
+template <int TM, int TN, int STAGES, bool F16, bool CHUNKS, class Epi>
 static void launch_conv_tile(const ConvArgs& a, Epi epi, hipStream_t st) {
   const int grid = (a.ntiles + 7) / 8 * 8;
-  ring_mma_kernel<TM, TN, STAGES, F16, Epi><<<grid, 256, 0, st>>>(a, epi);
+  // The DownSamples left to the ring kernel in CHUNKS order are small, and that order's addresses cost more: with feeding
+  // wavefronts, in tiles of 128 x 64, 1280 channels on 8 x 8 141 -> 126 us, 320 channels 38 -> 33.
+  constexpr bool WS = CHUNKS && TM * TN <= 2;
+  ring_mma_kernel<TM, TN, STAGES, F16, Epi, WS, CHUNKS><<<grid, WS ? 512 : 256, 0, st>>>(a, epi);
 }
 
 // Column tiles of the convolution kernel: the candidate width that pads the output channels least,
@@ -138,8 +141,8 @@ static int halo_plan(int B, int F, int O, int H, int W, int Wi, int mode) {
 }
 
 // halo_nblk > 0: conv_halo_kernel.  Else row tiles of 256 tokens when that still gives every CU two blocks, or of 128.  M output
-// tokens on an H x W map; (Hi, Wi, mode) describe the source map (see ConvArgs).
-template <bool F16, class Epi>
+// tokens on an H x W map; (Hi, Wi, mode) describe the source map (see ConvArgs).  CHUNKS: the order of the sums (ring_mma_kernel).
+template <bool F16, bool CHUNKS = false, class Epi>
 static si_status launch_conv3x3(const char* stage, const void* act, const void* wf, int64_t M, int C, int TN, int ncol, int H,
                                 int W, int Hi, int Wi, int mode, Epi epi, hipStream_t st, int O = 0, int ntaps = 9, int halo_nblk = 0) {
   StageScope scope(stage, st);
@@ -156,14 +159,14 @@ static si_status launch_conv3x3(const char* stage, const void* act, const void* 
   const bool big = rows2 * ncol >= SI_CONV_BIG_MIN;
   a.ntiles = (int)((big ? rows2 : (M + 127) / 128) * ncol);
   switch (TN * 2 + (big ? 1 : 0)) {
-    case 11: launch_conv_tile<2, 5, 3, F16>(a, epi, st); break;
-    case 10: launch_conv_tile<1, 5, 4, F16>(a, epi, st); break;
-    case 9: launch_conv_tile<2, 4, 3, F16>(a, epi, st); break;
-    case 8: launch_conv_tile<1, 4, 4, F16>(a, epi, st); break;
-    case 5: launch_conv_tile<2, 2, 4, F16>(a, epi, st); break;
-    case 4: launch_conv_tile<1, 2, 4, F16>(a, epi, st); break;
-    case 3: launch_conv_tile<2, 1, 4, F16>(a, epi, st); break;
-    case 2: launch_conv_tile<1, 1, 4, F16>(a, epi, st); break;
+    case 11: launch_conv_tile<2, 5, 3, F16, CHUNKS>(a, epi, st); break;
+    case 10: launch_conv_tile<1, 5, 4, F16, CHUNKS>(a, epi, st); break;
+    case 9: launch_conv_tile<2, 4, 3, F16, CHUNKS>(a, epi, st); break;
+    case 8: launch_conv_tile<1, 4, 4, F16, CHUNKS>(a, epi, st); break;
+    case 5: launch_conv_tile<2, 2, 4, F16, CHUNKS>(a, epi, st); break;
+    case 4: launch_conv_tile<1, 2, 4, F16, CHUNKS>(a, epi, st); break;
+    case 3: launch_conv_tile<2, 1, 4, F16, CHUNKS>(a, epi, st); break;
+    case 2: launch_conv_tile<1, 1, 4, F16, CHUNKS>(a, epi, st); break;
     default: return SI_ERR_SHAPE;
   }
   SI_CHECK_LAUNCH();
@@ -308,25 +311,46 @@ static si_status run_resblock(const ResPlan& p, const si_tensor5* x, const si_re
 
 struct ResamplePlan {
   int B, C, F, Hi, Wi, Ho, Wo, mode, TN, ncol, halo;
-  bool down;  // conv_down_kernel: every window in one launch, no operand buffer
+  bool chunks;  // DownSample that either kernel takes, with the same bits: sums in conv_down_kernel's order
+  bool down;    // conv_down_kernel: every window in one launch, no operand buffer
   int64_t Pi, Po, slice_len, Mi_max;
   int lanes;
   size_t lane_stride, off_a, off_w, weights_bytes, total_bytes;
 };
 
-// Whether a DownSample runs on conv_down_kernel: channels in whole column tiles of 320 (the only form built; 256- and
-// 512-channel networks stay on the ring kernel), patches that fit LDS (maps up to some 180 wide), four positions to load.
-// Measured over 320 .. 1280 channels, 9 x 11 .. 72 x 128 maps, 6 .. 25 frames, windows of 1 and 2: 1.3 .. 2.9 times the ring
-// kernel's speed, the small and odd maps included.
+// Whether conv_down_kernel can take a DownSample: channels in whole column tiles of 320 (the only form built; 256- and
+// 512-channel networks stay on the ring kernel), patches that fit LDS (maps up to some 180 wide), four positions to load.  Such
+// calls sum in its order on the ring kernel as well (ring_mma_kernel's CHUNKS), so that every slicing gives the same bits.
 static bool down_fits(const ResamplePlan& p) {
-  const int64_t ntile = (p.Po + kDownTokens - 1) / kDownTokens, nwg = (int64_t)p.B * p.F * ntile * (p.C / (32 * kDownTN));
-  if (p.C % (32 * kDownTN) || p.Pi < 4 || nwg >= 1 << 30) return false;
-  for (int64_t t = 0; t < ntile; ++t) {
+  if (p.C % (32 * kDownTN) || p.Pi < 4) return false;
+  for (int64_t m0 = 0; m0 < p.Po; m0 += kDownTokens) {
     int s0, n;
-    down_patch((int)(t * kDownTokens), (int)((t + 1) * kDownTokens < p.Po ? (t + 1) * kDownTokens : p.Po) - 1, p.Wi, p.Wo, &s0, &n);
+    down_patch((int)m0, (int)(m0 + kDownTokens < p.Po ? m0 + kDownTokens : p.Po) - 1, p.Wi, p.Wo, &s0, &n);
     if (n > 4 * kDownGroups) return false;
   }
   return true;
+}
+
+// Whether conv_down_kernel, all windows in one launch, beats the ring kernel, one window after the other.  A workgroup of the
+// former takes 70 us per 320 channels however few of its 256 outputs exist (a tile never straddles images), and a round of
+// them a little more the fuller it is.  A window of the latter takes about a third of that while it leaves CUs idle, then as
+// long as its contraction, and a pass over the source besides; from eight windows on two are in flight.  In units of 70 us
+// per 320 channels, fitted to 167 calls of 320 .. 2560 channels, 2 x 2 .. 72 x 128 maps and 1 .. 25 windows; of those the rule
+// takes the slower kernel in two, by 4 and 1 %.  Whole calls, ring -> conv_down (us): 1280 channels, 8 x 8, 25 x 2 frames,
+// unsliced 110 -> 298, in 7 windows 574 -> 330, in 25 windows 1118 -> 324; 640 channels, 36 x 64, 25 x 2 frames, unsliced
+// 299 -> 324, in 7 windows 444 -> 320; 320 channels, 64 x 64, one frame 31 -> 82; 72 x 128, 25 x 2 frames, unsliced 340 -> 206.
+static bool down_pays(const ResamplePlan& p, int64_t n_slices) {
+  const double per_token = p.C / 320.0 / kDownTokens;  // workgroups' worth of an output token
+  const int64_t nwg = (int64_t)p.B * p.F * ((p.Po + kDownTokens - 1) / kDownTokens) * (p.C / (32 * kDownTN));
+  if (nwg > (1 << 23) - 8) return false;  // a launch has fewer than 2^32 threads
+  const double down = 1.08 * (double)((nwg + 255) / 256) + 0.25 * (double)nwg / 256;
+  auto window = [&](int64_t frames) {
+    const double t = 0.23 + (double)(p.B * frames * p.Po) * per_token / 145;
+    return (t > 0.35 ? t : 0.35) + 14.0 / p.C;  // 3 us of launches
+  };
+  const double windows = (double)(n_slices - 1) * window(p.slice_len) + window(p.F - (n_slices - 1) * p.slice_len);
+  const double ring = windows * (n_slices >= 8 ? 0.55 : 1.0) + (double)p.B * p.F * p.Po / 68500;
+  return down < ring;
 }
 
 static si_status make_resample_plan(const si_tensor5* x, int32_t kind, int64_t slice_len, ResamplePlan* p) {
@@ -348,7 +372,8 @@ static si_status make_resample_plan(const si_tensor5* x, int32_t kind, int64_t s
   if ((double)p->Mi_max * p->C * 2.0 + 4096.0 >= 4294967296.0) return SI_ERR_SHAPE;  // 32-bit operand offsets
   if ((int64_t)p->B * p->slice_len * p->Po >= (1LL << 31) / 16) return SI_ERR_SHAPE;
   const int64_t n_slices = (p->F + p->slice_len - 1) / p->slice_len;
-  p->down = p->mode == kConvStride2 && down_fits(*p);
+  p->chunks = p->mode == kConvStride2 && down_fits(*p);
+  p->down = p->chunks && down_pays(*p, n_slices);
   p->lanes = n_slices >= 8 && !p->down ? 2 : 1;
   p->halo = p->mode == kConvNearestUp ? halo_plan(p->B, p->F, p->C, p->Ho, p->Wo, p->Wi, p->mode) : 0;
   if (p->down) {
@@ -384,8 +409,9 @@ static si_status run_resample(const ResamplePlan& p, const si_tensor5* x, const 
     StageScope scope("pack_weights", st0);
     const int64_t elems = (int64_t)p.ncol * 9 * (C / 32) * 2 * p.TN * 512;
     unsigned* z0 = reinterpret_cast<unsigned*>(ws + p.off_a);
-    pack_conv_kernel<false><<<(unsigned)((elems + 255) / 256), 256, 0, st0>>>(static_cast<const bf16*>(w_conv), wf, C, C, p.TN,
-                                                                             p.ncol, z0, p.down ? 0 : p.lanes, (int64_t)p.lane_stride);
+    auto pack = p.chunks ? pack_conv_kernel<false, true> : pack_conv_kernel<false, false>;
+    pack<<<(unsigned)((elems + 255) / 256), 256, 0, st0>>>(static_cast<const bf16*>(w_conv), wf, C, C, p.TN, p.ncol, z0,
+                                                          p.down ? 0 : p.lanes, (int64_t)p.lane_stride, 0, 9);
     SI_CHECK_LAUNCH();
   }
   if (p.down) {
@@ -418,8 +444,12 @@ static si_status run_resample(const ResamplePlan& p, const si_tensor5* x, const 
       SI_CHECK_LAUNCH();
     }
     EpiStoreRows epi{OUT, static_cast<const bf16*>(b_conv), win_out};
-    SI_TRY(launch_conv3x3<false>(p.mode == kConvStride2 ? "conv_down" : "conv_up", a, wf, (int64_t)p.B * Fw * p.Po, C, p.TN,
-                                 p.ncol, p.Ho, p.Wo, p.Hi, p.Wi, p.mode, epi, st, 0, 9, p.halo));
+    const int64_t Mo = (int64_t)p.B * Fw * p.Po;
+    if (p.chunks)
+      SI_TRY((launch_conv3x3<false, true>("conv_down", a, wf, Mo, C, p.TN, p.ncol, p.Ho, p.Wo, p.Hi, p.Wi, p.mode, epi, st)));
+    else
+      SI_TRY(launch_conv3x3<false>(p.mode == kConvStride2 ? "conv_down" : "conv_up", a, wf, Mo, C, p.TN, p.ncol, p.Ho, p.Wo, p.Hi,
+                                   p.Wi, p.mode, epi, st, 0, 9, p.halo));
   }
   if (lanes == 2) SI_TRY(lanes_join(aux, lanes, st0));
   return SI_OK;

@@ -28,3 +28,24 @@ def test_against_oracle(shape):
     _check(f"down {shape}", got, oracle.downsample_ref(x, w, b))
     if shape[2] > 1:
         assert np.array_equal(got, _run(x, w, b, "down", shape[2]))
+
+
+@pytest.mark.parametrize("shape", [
+    (1, 320, 9, 2, 2), (2, 320, 9, 5, 7), (1, 320, 9, 1, 6), (1, 320, 9, 33, 37), (1, 640, 9, 17, 30), (1, 320, 9, 12, 176),
+    (1, 1280, 9, 9, 11),        # four column tiles
+    (1, 960, 8, 24, 20),        # three; 128 x 64 tiles on the ring kernel
+    (2, 320, 16, 40, 40),       # 128 x 160 tiles there: 12800 outputs
+    (4, 640, 30, 32, 34),       # 256 x 160: 32640 outputs in half-empty tiles
+])
+def test_many_windows_and_one_agree(shape):
+    """One window per frame runs on conv_down_kernel, an unsliced call of these sizes on the ring kernel, in the same order."""
+    import torch
+    import paper_2411_01171_amd as si
+    x, w, b = _inputs(*shape, seed=sum(shape))
+    xd = torch.empty(shape, dtype=torch.bfloat16, device="cuda")
+    need = [si.si_resample_workspace_bytes(xd, si.SI_RESAMPLE_DOWN, n) for n in (1, shape[2])]
+    assert need[0] == 18 * shape[1] ** 2 < need[1]
+    got = _run(x, w, b, "down", 1)
+    assert np.array_equal(got, _run(x, w, b, "down", shape[2]))
+    last = slice(shape[2] - 1, shape[2])
+    _check(f"down {shape}", got[:, :, last], oracle.downsample_ref(x[:, :, last], w, b))
