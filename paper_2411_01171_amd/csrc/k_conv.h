@@ -99,10 +99,58 @@ template <class Epi>
 struct epi_slice_out<Epi, std::enable_if_t<Epi::kSliceOut>> : std::true_type {};
 
 // Slice-out of a tile of TOK tokens x TN blocks of 32 channels by NT threads: block i goes through LDS (patch[channel][token],
-// two buffers at lds, write(i, patch) fills one), and what it adds is in flight before the first of them is written: loads
-// behind each block's barrier had made a tile wait for memory once per block.  Maps and windows of whole 8-token
-// pieces move 16 bytes at a time; others (ragged) pairs of tokens, a wavefront 128 consecutive tokens of one channel, because
-// 16-byte accesses off their alignment are slower than 2-byte ones (45 x 50 positions, 7000 tokens x 640 channels: 51 and 36 us).
+// two buffers at lds, write(i, patch) fills one), and what it adds is in flight before the block is written: loads
+// behind each block's barrier had made a tile wait for memory once per block.
+// Maps and windows of whole 8-token pieces move 16 bytes at a time, requested for all blocks at once (slice_out_rows).  The others
+// are ragged: 16-byte accesses off their alignment are slower than 2-byte ones, so a lane moves V neighbouring tokens of a channel,
+// a pair where every offset is even, else one, and requests a block's while the one before is on its way.  One value after the
+// other behind the barrier, 2048 tokens x 640 channels of a 31 x 33 map took 49 us in proj_out (64 workgroups), like this 21;
+// 7000 tokens of a 45 x 50 map 34 and 18, 32736 tokens of the former 100 and 59.
+template <int V, int TN, int TOK, int NT, class Epi, class Write>
+__device__ __forceinline__ void slice_out_ragged(char* lds, const Epi& epi, int64_t m0, int64_t M, int n_first, int N, Write write) {
+  constexpr int LDP = TOK + 4, BUF = 32 * LDP * 4;
+  constexpr int CH = NT * V / TOK, NU = 32 / CH;  // channels at a time, pieces of a block per thread
+  using Piece = std::conditional_t<V == 2, unsigned, unsigned short>;
+  const int tid = threadIdx.x;
+  const int tok = tid % (TOK / V) * V, c0 = __builtin_amdgcn_readfirstlane(tid / (TOK / V));  // a wavefront's lanes share a channel
+  const bool inside = m0 + tok < M;  // of a pair both or none: M is even
+  const int64_t at = epi.place(inside ? m0 + tok : 0);
+  Piece x[2][NU];
+  float bias[2];  // lane l: of channel l % 32 of the block
+  auto request = [&](int i) {
+    const int b = n_first + 32 * i;
+    bias[i & 1] = param_or(epi.bias, b + tid % 32 < N ? b + tid % 32 : 0, 0.f);
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+      const int n = b + c0 + CH * u;
+      x[i & 1][u] = *reinterpret_cast<const Piece*>(epi.x + at + epi.channel(n < N ? n : 0));
+    }
+  };
+  request(0);
+#pragma unroll
+  for (int i = 0; i < TN; ++i) {
+    float* patch = reinterpret_cast<float*>(lds + (i & 1) * BUF);
+    write(i, patch);
+    if (i + 1 < TN) request(i + 1);
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+      const int ch = c0 + CH * u, n = n_first + 32 * i + ch;
+      const float bn = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(bias[i & 1]), ch));
+      if (!inside || n >= N) continue;
+      const Piece xv = x[i & 1][u];
+      Piece* o = reinterpret_cast<Piece*>(epi.out + at + epi.channel(n));
+      if constexpr (V == 2) {
+        const float2 v = *reinterpret_cast<const float2*>(patch + ch * LDP + tok);
+        const float r0 = __uint_as_float(xv << 16) + (v.x + bn), r1 = __uint_as_float(xv & 0xffff0000u) + (v.y + bn);
+        *o = (unsigned)float_to_bf16_bits(r0) | ((unsigned)float_to_bf16_bits(r1) << 16);
+      } else {
+        *o = float_to_bf16_bits(__uint_as_float((unsigned)xv << 16) + (patch[ch * LDP + tok] + bn));
+      }
+    }
+  }
+}
+
 template <int TN, int TOK, int NT, class Epi, class Write>
 __device__ __forceinline__ void slice_out_rows(char* lds, const Epi& epi, int64_t m0, int64_t M, int n_first, int N, Write write) {
   constexpr int LDP = TOK + 4, BUF = 32 * LDP * 4;
@@ -144,33 +192,10 @@ __device__ __forceinline__ void slice_out_rows(char* lds, const Epi& epi, int64_
         *reinterpret_cast<u32x4_t*>(epi.out + at + epi.channel(n)) = o;
       }
     }
+  } else if (epi.pairs()) {
+    slice_out_ragged<2, TN, TOK, NT>(lds, epi, m0, M, n_first, N, write);
   } else {
-    constexpr int PER = TOK / 128, CH = NT / kWave / PER;
-    const int wave = tid / kWave, tok = wave % PER * 128 + tid % kWave * 2, c0 = wave / PER;
-    const int64_t left = M - m0 - tok;
-    const int64_t a0 = epi.place(left > 0 ? m0 + tok : 0), a1 = epi.place(left > 1 ? m0 + tok + 1 : 0);
-    const bool joined = left > 1 && a1 == a0 + 1;  // neighbours
-#pragma unroll
-    for (int i = 0; i < TN; ++i) {
-      write(i, patch(i));
-      __syncthreads();
-      const int n1 = n_first + 32 * (i + 1) < N ? 32 : N - n_first - 32 * i;
-#pragma unroll 4
-      for (int ch = c0; ch < n1; ch += CH) {  // a short loop: unrolled over the blocks as well, its code takes longer to arrive than to run
-        const int n = n_first + 32 * i + ch;
-        const float2 v = *reinterpret_cast<const float2*>(patch(i) + ch * LDP + tok);
-        const float bn = param_or(epi.bias, n, 0.f);
-        const int64_t o0 = a0 + epi.channel(n), o1 = a1 + epi.channel(n);
-        if (joined && (o0 & 1) == 0) {
-          const unsigned xw = *reinterpret_cast<const unsigned*>(epi.x + o0);
-          const float r0 = __uint_as_float(xw << 16) + (v.x + bn), r1 = __uint_as_float(xw & 0xffff0000u) + (v.y + bn);
-          *reinterpret_cast<unsigned*>(epi.out + o0) = (unsigned)float_to_bf16_bits(r0) | ((unsigned)float_to_bf16_bits(r1) << 16);
-        } else {
-          if (left > 0) epi.out[o0] = from_float<bf16>(to_float(epi.x[o0]) + (v.x + bn));
-          if (left > 1) epi.out[o1] = from_float<bf16>(to_float(epi.x[o1]) + (v.y + bn));
-        }
-      }
-    }
+    slice_out_ragged<1, TN, TOK, NT>(lds, epi, m0, M, n_first, N, write);
   }
 }
 
@@ -565,8 +590,9 @@ struct EpiSliceOutRows {
   bf16* out;
   const bf16* bias;
   Window w;
-  // What slice_out_rows asks.  !ragged(): eight tokens are always aligned positions of one image.
+  // What slice_out_rows asks.  !ragged(): eight tokens are always aligned positions of one image; pairs(): two are.
   __device__ __forceinline__ bool ragged() const { return ((w.P | w.p0 | w.Pw) & 7) != 0; }
+  __device__ __forceinline__ bool pairs() const { return ((w.P | w.p0 | w.Pw) & 1) == 0; }
   __device__ __forceinline__ int64_t place(int64_t m) const {  // of token m, channel 0
     const int mi = (int)m, bf = mi / w.Pw;
     return ((int64_t)(bf / w.Fw) * w.C * w.F + (w.f0 + bf % w.Fw)) * w.P + w.p0 + mi % w.Pw;
