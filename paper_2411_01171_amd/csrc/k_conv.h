@@ -924,37 +924,13 @@ __global__ __launch_bounds__(256) void window_to_tokens_silu_kernel(const bf16* 
   const int b = bf / w.Fw, fl = bf % w.Fw, f = w.f0 + fl;
   const int pt = blockIdx.x * 64, ct = blockIdx.y * 64;
   const int ng = w.C / w.G;
-  if (pt + 64 <= w.Pw && ct + 64 <= w.C) {
-    const SliceTile t = load_slice_tile<bf16>(x, RAW ? nullptr : stats, RAW ? nullptr : gamma, RAW ? nullptr : beta, w, b, f, pt, ct, ng);
+  const SliceTile t = load_slice_tile(x, RAW ? nullptr : stats, RAW ? nullptr : gamma, RAW ? nullptr : beta, w, b, f, pt, ct, ng);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const float ga = t.ga[i] * t.rstd[i];
+  for (int i = 0; i < 4; ++i) {
+    const float ga = t.ga[i] * t.rstd[i];
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
-        tile[threadIdx.x / 16 + 16 * i][threadIdx.x % 16 * 4 + j] = RAW ? t.x(i, j) : silu((t.x(i, j) - t.mean[i]) * ga + t.be[i]);
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int id = threadIdx.x + i * 256, cl = id / 16, pq = (id % 16) * 4;
-      const int c = ct + cl, pl = pt + pq;
-      float v[4] = {0.f, 0.f, 0.f, 0.f};
-      if (c < w.C && pl < w.Pw) {
-        float mean = 0.f, ga = 1.f, be = 0.f;
-        if constexpr (!RAW) {
-          const int g = c / ng;
-          mean = stats[(((int64_t)b * w.F + f) * w.G + g) * 2 + 0];
-          ga = param_or(gamma, c, 1.f) * stats[(((int64_t)b * w.F + f) * w.G + g) * 2 + 1];
-          be = param_or(beta, c, 0.f);
-        }
-        const bf16* src = x + (((int64_t)b * w.C + c) * w.F + f) * w.P + w.p0 + pl;
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          if (pl + j < w.Pw) v[j] = RAW ? to_float(src[j]) : silu((to_float(src[j]) - mean) * ga + be);
-      }
-#pragma unroll
-      for (int j = 0; j < 4; ++j) tile[cl][pq + j] = v[j];
-    }
+    for (int j = 0; j < 4; ++j)
+      tile[threadIdx.x / 16 + 16 * i][threadIdx.x % 16 * 4 + j] = RAW ? t.x(i, j) : silu((t.x(i, j) - t.mean[i]) * ga + t.be[i]);
   }
   __syncthreads();
 #pragma unroll

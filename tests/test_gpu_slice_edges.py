@@ -1,11 +1,54 @@
-"""Slice-out of windows that are no whole 16-byte pieces: odd maps (one token per lane), even ones (pairs)."""
+"""Slice-in and slice-out where windows are no whole 64 x 64 tiles and no whole 16-byte pieces: odd maps and windows (one token per
+lane), even ones (pairs), windows shorter than a tile, images of fewer than four positions, channels that end inside a tile --
+windows against the unsliced run bit for bit, and the unsliced run against the float64 oracle."""
 import numpy as np
 import pytest
 
+import oracle
 import si_workloads as wl
 from helpers import tiny_spec
 
 pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("C,heads,H,W,windows", [
+    (96, 3, 1, 1, (1,)),              # one position
+    (96, 3, 1, 2, (1,)),
+    (160, 5, 1, 3, (1, 2)),
+    (32, 1, 2, 2, (1, 3)),
+    (96, 3, 5, 13, (1, 3, 16, 64)),   # 65 positions: a tile and one more; odd channel rows
+    (160, 5, 7, 9, (4, 17, 32, 62)),  # a tile less one
+    (96, 3, 10, 13, (6, 33, 65)),     # even map, even and odd windows
+    (640, 10, 9, 15, (16, 45, 64)),
+])
+def test_block_windows(C, heads, H, W, windows):
+    from gpu_helpers import errors, run_block
+    spec = tiny_spec(wl.TEMPORAL, B=2, C=C, F=3, H=H, W=W, heads=heads, dim_head=C // heads, groups=32, dtype="bf16")
+    x, w = wl.make_x(spec), wl.make_weights(spec, randomize_affine=True)
+    whole = run_block(spec, x, w, None, H * W)
+    e = errors(whole, oracle.block_forward_ref(x, w, spec, None), x)
+    print(e)
+    assert e["max_abs"] <= 2e-2 and e["rel_l2"] <= 5e-3
+    for n in windows:
+        assert np.array_equal(run_block(spec, x, w, None, n), whole), n
+
+
+@pytest.mark.parametrize("kw,windows", [
+    (dict(C=96, F=5, H=1, W=3), (1, 2)),
+    (dict(C=160, F=4, H=5, W=13), (1, 3)),
+    (dict(C=160, C_out=96, F=3, H=9, W=9, temb_dim=0), (1,)),
+])
+def test_resblock_windows(kw, windows):
+    from gpu_helpers import errors, run_resblock
+    spec = wl.scaled(wl.RES_CONFIGS["res1"], **kw)
+    x, w, temb = wl.make_x(spec), wl.make_res_weights(spec, randomize_affine=True), wl.make_temb(spec)
+    whole = run_resblock(spec, x, w, temb, spec.F)
+    ref = oracle.resblock_forward_ref(x, w, spec, temb)
+    e = errors(whole, ref, x if x.shape == ref.shape else np.zeros_like(ref))
+    print(e)
+    assert e["max_abs"] <= 2e-2 and e["rel_l2"] <= 5e-3
+    for n in windows:
+        assert np.array_equal(run_resblock(spec, x, w, temb, n), whole), n
 
 
 def test_resblock_large_row_tiles():
