@@ -89,6 +89,20 @@ struct RingDims {
 struct RingShape {
   int tn, ncol;
 };
+// Whether a GEMM runs in gemm_160_kernel's tiles (k_gemm_wide.h).  They need a workgroup for three quarters of the CUs, over the
+// windows in flight, to beat narrower tiles on the ring kernel, however many more those are.  Per launch alone, narrow -> 160 (us):
+// N = K = 640 on 7000 tokens (220 workgroups) 18.5 -> 15.2, K = 2560 41 -> 32; N = K = 1280 on 2048 tokens (128) 17.2 -> 18.4,
+// K = 5120 37 -> 44.  N = K = 640 on 2048 tokens, 64 workgroups, 9 -> 12, but with three windows in flight (192 of 256 CUs) the
+// block of them 1375 -> 1341.
+// Fewer than ten stages of 64 channels only spread the prologue over a window of up to 9216 tokens.  Past it the ring kernel's
+// rounds are full as well, and the clock that these launches leave to the attention behind them is lower.  Whole blocks of 320
+// channels, ring -> 160 (us), spatial with heads of 40: 8192 tokens per window 9261 -> 8817, 9216 (48 x 48) 3396 -> 3344, 11616
+// (44 x 44) 3624 -> 3938, 32768 9049 -> 9369; temporal with heads of 80: 16384 tokens 169 -> 171, 20000 780 -> 802, 20480
+// 179 -> 192, 65536 458 -> 465.
+static bool tiles_of_160(RingDims d, int N, int K) {
+  if (K % 64 || N % 160) return false;
+  return (d.Mmax + 127) / 128 * (N / 160) * d.lanes >= 190 && (K >= 640 || d.Mmax <= 9216);
+}
 static RingShape ring_shape(RingDims d, int N, int K) {
   // q/k/v of one window in flight at the deep levels (N = 3 K = 3840 on 2048 tokens): 128-column tiles make
   // 480 workgroups, two for nearly every CU, where 160-column tiles make 384 (measured 34.0 -> 31.5 us)
@@ -104,11 +118,7 @@ static RingShape ring_shape(RingDims d, int N, int K) {
     if (rows128 * ((N + 63) / 64) > 256 && rows128 * nc3 <= 256 && rows128 * nc3 > 160 && (int64_t)nc3 * 96 * 10 <= (int64_t)N * 11)
       return RingShape{3, nc3};
   }
-  // gemm_160_kernel (k_gemm_wide.h) needs a workgroup for three quarters of the CUs, over the windows in flight, to beat narrower
-  // tiles on the ring kernel, however many more those are.  Per launch alone, narrow -> 160 (us): N = K = 640 on 7000 tokens (220
-  // workgroups) 18.5 -> 15.2, K = 2560 41 -> 32; N = K = 1280 on 2048 tokens (128) 17.2 -> 18.4, K = 5120 37 -> 44.  N = K = 640 on
-  // 2048 tokens, 64 workgroups, 9 -> 12, but with three windows in flight (192 of 256 CUs) the block of them 1375 -> 1341.
-  if (K % 64 == 0 && N % 160 == 0 && (d.Mmax + 127) / 128 * (N / 160) * d.lanes >= 190) return RingShape{5, N / 160};
+  if (tiles_of_160(d, N, K)) return RingShape{5, N / 160};
   const int64_t rows = (d.Mmax + 127) / 128 * (K > 512 ? d.lanes : 1);
   const int min_wg = K > 512 ? 330 : 400;
   RingShape best{1, (N + 31) / 32};
@@ -432,7 +442,7 @@ static si_status launch_gemm_ring(const char* stage, const void* act, const void
   // columns on 2048 tokens: 512 tiles of 256 x 160 took 61 us, 256 of these 47), else as before.  Other GEMMs with three slots,
   // one workgroup per CU, or, where there is a second one for it and the epilogue needs no more, two slots and two workgroups
   // (q/k/v at 640 channels on 7000 tokens 32 -> 28.7 us).
-  if (rs.tn == 5 && N % 160 == 0 && K % 64 == 0) {
+  if (rs.tn == 5 && tiles_of_160(Mmax, N, K)) {
     auto launch = [&](auto wc, auto tm, auto slots) {
       constexpr int WC = decltype(wc)::value, TM = decltype(tm)::value;
       a.ncol = N / (160 * WC);

@@ -28,3 +28,14 @@ def test_long_and_short_windows_agree(kind, kw, long, short, against_oracle):
         e = errors(a, oracle.block_forward_ref(x, w, spec, c), x)
         print(e)
         assert e["max_abs"] <= 2e-2 and e["rel_l2"] <= 5e-3
+
+
+@pytest.mark.parametrize("C", [64, 128])
+def test_fewer_stages_than_slots(C):
+    """proj_in over 64 and 128 channels: one and two stages for three slots.  Windows of 8064 tokens, two in flight, run in tiles of
+    160 columns, those of 1024 on the ring kernel (from 8192 tokens the LayerNorm sums in another order)."""
+    from gpu_helpers import run_block
+    spec = tiny_spec(wl.TEMPORAL, B=1, C=C, F=16, H=64, W=64, heads=5, dim_head=64, groups=32, dtype="bf16")
+    x, w = wl.make_x(spec), wl.make_weights(spec, randomize_affine=True)
+    a, b = run_block(spec, x, w, None, 504), run_block(spec, x, w, None, 64)
+    assert np.all(np.isfinite(a)) and np.array_equal(a, b)
