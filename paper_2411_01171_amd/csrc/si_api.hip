@@ -586,24 +586,17 @@ static si_status launch_layer_norm(const char* stage, const float* h, T* a, int6
       const unsigned wgs = (unsigned)((M + 7) / 8);
       const bf16 *gp = static_cast<const bf16*>(g), *bp = static_cast<const bf16*>(b);
       bf16* ap = reinterpret_cast<bf16*>(a);
-      // large windows at the widths of the five configurations run on the eight-rows-per-wavefront
-      // kernel; with few rows one wavefront per row keeps more of the chip busy (measured at 2048
-      // rows: 9 us against 15 at D = 640, 12 against 25 at D = 1280; at 18432 rows, D = 320: 21 against 14),
-      // eight rows per workgroup so that the stores are whole 128-byte pieces (2048 rows: 9.3 -> 7.9 us
-      // at D = 640, 12.2 -> 9.6 at D = 1280)
-      switch (M >= 8192 ? D : 0) {
-        case 320: layer_norm_frag_kernel<10><<<wgs, 64, 0, st>>>(h, ap, M, gp, bp, eps, pe, Pw, Fw, f0); break;
-        case 640: layer_norm_frag_kernel<20><<<wgs, 64, 0, st>>>(h, ap, M, gp, bp, eps, pe, Pw, Fw, f0); break;
-        case 1280: layer_norm_frag_kernel<40><<<wgs, 64, 0, st>>>(h, ap, M, gp, bp, eps, pe, Pw, Fw, f0); break;
-        default:
-          if (D % 8 == 0 && D <= 2048 && (!g || aligned16(g)) && (!b || aligned16(b)))
-            row_dispatch((D + 255) / 256, [&](auto nq) {
-              layer_norm_rows8_kernel<nq.value><<<wgs, 512, 0, st>>>(h, ap, M, D, gp, bp, eps, pe, Pw, Fw, f0);
-            });
-          else
-            layer_norm_kernel<T, sizeof(T) == 2><<<blocks, 256, 0, st>>>(h, a, M, D, static_cast<const T*>(g), static_cast<const T*>(b),
-                                                                         eps, pe, Pw, Fw, f0);
-      }
+      // One kernel for windows of every size, so that a row's sums, and the result's bits, do not depend on the window.  It is also the
+      // fastest: one wavefront per eight rows, loads of the eight in flight together, took (us, it -> rows8) 11.4 -> 9.5 on 8192
+      // rows of 320 columns, 18.2 -> 12.3 of 640, 37.9 -> 19.5 of 1280; on 18432 rows 14.4 -> 12.8, 24.4 -> 19.3, 60 -> 33; on
+      // 65536 rows 30.0 and 30.0, 56.4 and 56.1, 155 -> 118.
+      if (D % 8 == 0 && D <= 2048 && (!g || aligned16(g)) && (!b || aligned16(b)))
+        row_dispatch((D + 255) / 256, [&](auto nq) {
+          layer_norm_rows8_kernel<nq.value><<<wgs, 512, 0, st>>>(h, ap, M, D, gp, bp, eps, pe, Pw, Fw, f0);
+        });
+      else
+        layer_norm_kernel<T, sizeof(T) == 2><<<blocks, 256, 0, st>>>(h, a, M, D, static_cast<const T*>(g), static_cast<const T*>(b),
+                                                                     eps, pe, Pw, Fw, f0);
     }
   }
   else

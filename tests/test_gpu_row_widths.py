@@ -26,3 +26,13 @@ def test_widths_and_alignments(D):
     bound = 2.0 ** (np.floor(np.log2(np.abs(ref).max())) - 8) + 6 * 2.0 ** -8 * np.sqrt(np.mean((ref - x) ** 2))
     print(e, "bound", bound)
     assert e["max_abs"] <= bound and e["rel_l2"] <= 5e-3
+
+
+@pytest.mark.parametrize("C,D,heads", [(64, 320, 5), (640, 640, 10), (1280, 1280, 20)])
+def test_windows_of_many_rows_agree(C, D, heads):
+    """Windows of 16384 and of 8192 rows give the bits of windows of 1024."""
+    from gpu_helpers import run_block
+    spec = tiny_spec(wl.TEMPORAL, B=1, C=C, F=16, H=32, W=32, heads=heads, dim_head=D // heads, groups=32, dtype="bf16")
+    x, w = wl.make_x(spec), wl.make_weights(spec, randomize_affine=True)
+    a = run_block(spec, x, w, None, 64)
+    assert np.array_equal(run_block(spec, x, w, None, 512), a) and np.array_equal(run_block(spec, x, w, None, 1024), a)
