@@ -108,3 +108,13 @@ def test_live_bytes_bounded_by_one_slice():
     sliced = si.si_resblock_live_activation_bytes(x, wd, spec.slice_len)
     unsliced = si.si_resblock_live_activation_bytes(x, wd, spec.F)
     assert 0 < sliced <= unsliced / 4
+
+
+@pytest.mark.parametrize("width", [4096, 4100, 8200])
+def test_wide_embedding(width):
+    """Embeddings of one whole chunk of the projection's activations (4096), a little more, and two with a rest."""
+    from gpu_helpers import run_resblock
+    spec = wl.scaled(wl.RES_CONFIGS["res1"], F=2, H=5, W=6, temb_dim=width)
+    x, w, temb = wl.make_x(spec), wl.make_res_weights(spec, randomize_affine=True), wl.make_temb(spec)
+    got = run_resblock(spec, x, w, temb, 1)
+    _check(f"embedding of {width}", got, oracle.resblock_forward_ref(x, w, spec, temb), x)
