@@ -10,7 +10,8 @@ against a cached one.  Inputs are resident in HBM before the timed region.
 Prints ONE JSON line: whole-step throughput in algorithmic TFLOP/s, the
 roofline record of the dominant kernel (per-launch duration from HIP events
 recorded by the library around each launch), and the CPU oracle timed on a
-bounded sample of the same workload.
+bounded sample of the same workload.  The whole record, with the stage tables
+of every workload, goes to stderr.
 """
 from __future__ import annotations
 
@@ -250,7 +251,7 @@ def main_resblock(args):
             threads = len(os.sched_getaffinity(0))
         result["cpu_baseline"] = {"value": sub.flops() / dt / 1e12, "unit": "TFLOP/s", "cores": int(threads), "kind": "oracle",
                                   "sample": f"1 of {spec.F} frames (B={spec.B}); fp64 NumPy; 1 pass in {dt:.1f} s"}
-    print(json.dumps(result))
+    emit(result)
 
 
 def main_resample(args):
@@ -305,7 +306,7 @@ def main_resample(args):
     ach = w_flops / (c_ms / c_cnt * 1e-3) / 1e12
     stage_report[conv]["TFLOP/s"] = round(ach, 2)
     value = flops / (ms_per_step * 1e-3) / 1e12
-    print(json.dumps({
+    emit({
         "metric": "sliced block-forward TFLOP/s (% MFMA peak) + peak live activation bytes vs unsliced",
         "value": value, "unit": "TFLOP/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup, "ms_per_step": ms_per_step,
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "bf16", "data": "synthetic",
@@ -316,7 +317,30 @@ def main_resample(args):
         "roofline": {"bound": "mfma", "kernel": conv, "achieved": ach, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                      "frac": ach / PEAK_BF16_TFLOPS, "traffic": None, "avg_launch_us": c_ms / c_cnt * 1e3,
                      "algorithmic_flop_per_launch": w_flops},
-        "stages": stage_report}))
+        "stages": stage_report})
+
+
+def summary(record):
+    """What of a record fits the tail that a log keeps of a run (2000 characters): no stage tables, one short entry per workload."""
+    out = {k: v for k, v in record.items() if k not in ("stages", "per_block", "configs", "live_activation_bytes", "memory_check",
+                                                        "hbm_floor_check", "ms_reps", "rehash", "roofline", "cpu_baseline")}
+    if "live_activation_bytes" in record:
+        out["live_activation_bytes"] = {k: v for k, v in record["live_activation_bytes"].items() if k in ("sliced", "unsliced_same_kernels", "ratio")}
+    if "roofline" in record:
+        out["roofline"] = {k: v for k, v in record["roofline"].items()
+                           if k in ("bound", "kernel", "achieved", "peak", "unit", "frac", "avg_launch_us", "algorithmic_flop_per_launch")}
+    if "cpu_baseline" in record:
+        out["cpu_baseline"] = {k: v for k, v in record["cpu_baseline"].items() if k in ("value", "unit", "cores", "kind")}
+    if "configs" in record:
+        out["configs"] = {n: {"TFLOP/s": round(c["TFLOP/s"], 1), "ms": round(c["ms_per_step"], 4),
+                              "live": round(c["live_activation_bytes"]["ratio"], 3)} for n, c in record["configs"].items()}
+    return out
+
+
+def emit(record):
+    """One line on stdout; the whole record, stage tables included, as a line on stderr."""
+    print(json.dumps(record), file=sys.stderr, flush=True)
+    print(json.dumps(summary(record)), flush=True)
 
 
 def source_hash():
@@ -621,7 +645,7 @@ def main():
         result["configs"] = configs
     if not args.no_cpu_baseline:
         result["cpu_baseline"] = cpu_baseline(specs)
-    print(json.dumps(result))
+    emit(result)
 
 
 def main_rehash_probe(args):
@@ -666,7 +690,7 @@ def main_rehash_probe(args):
     stages = si.si_stage_timing_read()
     si.si_stage_timing_enable(False)
     value = spec.flops() / (ms_per_step * 1e-3) / 1e12
-    print(json.dumps({
+    emit({
         "metric": "sliced block-forward TFLOP/s (% MFMA peak) + peak live activation bytes vs unsliced",
         "value": value, "unit": "TFLOP/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup, "ms_per_step": ms_per_step,
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": spec.dtype, "data": "synthetic",
@@ -674,7 +698,7 @@ def main_rehash_probe(args):
                                f"FLOPs whether computed or handed back)", "algorithmic_flop_per_step": spec.flops()},
         "rehash": {"probe": args.rehash_probe, "reused": bool(probe["reused"]), "cos": probe["cos"]},
         "stages": {n: {"avg_us": round(ms / c * 1e3, 2), "launches_per_step": c / args.steps, "ms_per_step": round(ms / args.steps, 4)}
-                   for n, (ms, c) in stages.items()}}))
+                   for n, (ms, c) in stages.items()}})
 
 
 if __name__ == "__main__":
