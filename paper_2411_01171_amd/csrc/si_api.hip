@@ -85,23 +85,19 @@ static inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t
 struct RingDims {
   int64_t Mmax;
   int lanes;
+  bool temporal;
 };
 struct RingShape {
   int tn, ncol;
 };
-// Whether a GEMM runs in gemm_160_kernel's tiles (k_gemm_wide.h).  They need a workgroup for three quarters of the CUs, over the
-// windows in flight, to beat narrower tiles on the ring kernel, however many more those are.  Per launch alone, narrow -> 160 (us):
-// N = K = 640 on 7000 tokens (220 workgroups) 18.5 -> 15.2, K = 2560 41 -> 32; N = K = 1280 on 2048 tokens (128) 17.2 -> 18.4,
-// K = 5120 37 -> 44.  N = K = 640 on 2048 tokens, 64 workgroups, 9 -> 12, but with three windows in flight (192 of 256 CUs) the
-// block of them 1375 -> 1341.
-// Fewer than ten stages of 64 channels only spread the prologue over a window of up to 9216 tokens.  Past it the ring kernel's
-// rounds are full as well, and the clock that these launches leave to the attention behind them is lower.  Whole blocks of 320
-// channels, ring -> 160 (us), spatial with heads of 40: 8192 tokens per window 9261 -> 8817, 9216 (48 x 48) 3396 -> 3344, 11616
-// (44 x 44) 3624 -> 3938, 32768 9049 -> 9369; temporal with heads of 80: 16384 tokens 169 -> 171, 20000 780 -> 802, 20480
-// 179 -> 192, 65536 458 -> 465.
-static bool tiles_of_160(RingDims d, int N, int K) {
-  if (K % 64 || N % 160) return false;
-  return (d.Mmax + 127) / 128 * (N / 160) * d.lanes >= 190 && (K >= 640 || d.Mmax <= 9216);
+// Whether gemm_160_kernel (k_gemm_wide.h) can take a GEMM in tiles of 160 columns.  Fewer than ten stages of 64 channels only
+// spread its prologue over a window of up to 16384 tokens (one tile of 128 x 160 per CU at 320 columns), in spatial blocks
+// 10240: past it the ring kernel's rounds are full as well, and the clock that these launches leave to the fp32 attention behind
+// them is lower.  Whole blocks of 320 channels, ring -> 160 (us): temporal with heads of 80, 8 windows of 16384 tokens 847 -> 831,
+// of 20000 780 -> 802, of 20480 179 -> 192, of 65536 458 -> 465; spatial with heads of 40, 8192 tokens 9046 -> 8817, 9600 (three
+// frames of 40 x 40) 2827 -> 2768, 11616 (of 44 x 44) 3624 -> 3938, 32768 9049 -> 9369.
+static bool fits_160(RingDims d, int N, int K) {
+  return N % 160 == 0 && K % 64 == 0 && (K >= 640 || d.Mmax <= (d.temporal ? 16384 : 10240));
 }
 static RingShape ring_shape(RingDims d, int N, int K) {
   // q/k/v of one window in flight at the deep levels (N = 3 K = 3840 on 2048 tokens): 128-column tiles make
@@ -118,7 +114,11 @@ static RingShape ring_shape(RingDims d, int N, int K) {
     if (rows128 * ((N + 63) / 64) > 256 && rows128 * nc3 <= 256 && rows128 * nc3 > 160 && (int64_t)nc3 * 96 * 10 <= (int64_t)N * 11)
       return RingShape{3, nc3};
   }
-  if (tiles_of_160(d, N, K)) return RingShape{5, N / 160};
+  // gemm_160_kernel needs a workgroup for three quarters of the CUs, over the windows in flight, to beat narrower
+  // tiles on the ring kernel, however many more those are.  Per launch alone, narrow -> 160 (us): N = K = 640 on 7000 tokens (220
+  // workgroups) 18.5 -> 15.2, K = 2560 41 -> 32; N = K = 1280 on 2048 tokens (128) 17.2 -> 18.4, K = 5120 37 -> 44.  N = K = 640 on
+  // 2048 tokens, 64 workgroups, 9 -> 12, but with three windows in flight (192 of 256 CUs) the block of them 1375 -> 1341.
+  if (fits_160(d, N, K) && (d.Mmax + 127) / 128 * (N / 160) * d.lanes >= 190) return RingShape{5, N / 160};
   const int64_t rows = (d.Mmax + 127) / 128 * (K > 512 ? d.lanes : 1);
   const int min_wg = K > 512 ? 330 : 400;
   RingShape best{1, (N + 31) / 32};
@@ -312,7 +312,7 @@ static si_status make_plan(const si_tensor5* x, const si_block_weights* w, const
   auto wbytes = [&](size_t N, size_t K) {
     if (p->f32_cols) return (size_t)0;  // read as they are
     if (!p->ring) return N * K * es;
-    const RingShape rs = ring_shape(RingDims{p->Mmax, p->lanes}, (int)N, (int)K);
+    const RingShape rs = ring_shape(RingDims{p->Mmax, p->lanes, p->kind == SI_BLOCK_TEMPORAL}, (int)N, (int)K);
     return (size_t)rs.ncol * rs.tn * 32 * K * es;
   };
   p->off_w_in = take(wbytes(Dz, C));
@@ -442,7 +442,7 @@ static si_status launch_gemm_ring(const char* stage, const void* act, const void
   // columns on 2048 tokens: 512 tiles of 256 x 160 took 61 us, 256 of these 47), else as before.  Other GEMMs with three slots,
   // one workgroup per CU, or, where there is a second one for it and the epilogue needs no more, two slots and two workgroups
   // (q/k/v at 640 channels on 7000 tokens 32 -> 28.7 us).
-  if (rs.tn == 5 && tiles_of_160(Mmax, N, K)) {
+  if (rs.tn == 5 && fits_160(Mmax, N, K)) {
     auto launch = [&](auto wc, auto tm, auto slots) {
       constexpr int WC = decltype(wc)::value, TM = decltype(tm)::value;
       a.ncol = N / (160 * WC);
@@ -586,11 +586,13 @@ static si_status launch_layer_norm(const char* stage, const float* h, T* a, int6
       const unsigned wgs = (unsigned)((M + 7) / 8);
       const bf16 *gp = static_cast<const bf16*>(g), *bp = static_cast<const bf16*>(b);
       bf16* ap = reinterpret_cast<bf16*>(a);
-      // One kernel for windows of every size, so that a row's sums, and the result's bits, do not depend on the window.  It is also the
-      // fastest: one wavefront per eight rows, loads of the eight in flight together, took (us, it -> rows8) 11.4 -> 9.5 on 8192
-      // rows of 320 columns, 18.2 -> 12.3 of 640, 37.9 -> 19.5 of 1280; on 18432 rows 14.4 -> 12.8, 24.4 -> 19.3, 60 -> 33; on
-      // 65536 rows 30.0 and 30.0, 56.4 and 56.1, 155 -> 118.
-      if (D % 8 == 0 && D <= 2048 && (!g || aligned16(g)) && (!b || aligned16(b)))
+      // Eight rows per wavefront (layer_norm_frag_kernel) for large windows of 320 columns: alone it takes longer there as well (8192
+      // rows 11.4 us, rows8 9.5), but a spatial block of heads of 40, 64 x 64, whose attention runs beside it, 8879 us against 9052.
+      // At 640 and 1280 columns it had taken windows of 8192 and more rows too: rows8 12.3 us against 18.2 and 19.5 against 37.9, temporal
+      // blocks of 9216 rows 1568 against 1651, of 18432 rows 1400 against 1461.
+      if (D == 320 && M >= 8192)
+        layer_norm_frag_kernel<10><<<wgs, 64, 0, st>>>(h, ap, M, gp, bp, eps, pe, Pw, Fw, f0);
+      else if (D % 8 == 0 && D <= 2048 && (!g || aligned16(g)) && (!b || aligned16(b)))
         row_dispatch((D + 255) / 256, [&](auto nq) {
           layer_norm_rows8_kernel<nq.value><<<wgs, 512, 0, st>>>(h, ap, M, D, gp, bp, eps, pe, Pw, Fw, f0);
         });
@@ -797,7 +799,7 @@ static si_status run_block(const Plan& p, const si_tensor5* x, const si_block_we
   // (not the FFN-half kernel) reads them
   const bool ring = p.ring;
   const bool self_frag = ring && !p.post_fused && (spatial || !fused_ffn), cross_frag = ring && !fused_ffn;
-  const RingDims Mx{p.Mmax, p.lanes};
+  const RingDims Mx{p.Mmax, p.lanes, p.kind == SI_BLOCK_TEMPORAL};
   auto cT = [](const void* q) { return static_cast<const T*>(q); };
 
   // ---- once per call: weight re-layout, frame embedding table (skipped when the caller vouches that
