@@ -10,7 +10,7 @@
 // In the kernel, cycles: 669 per 16 channels of the first form (its MFMAs are 660) + 4.3 k prologue + 10.7 k epilogue (the GELU's
 // vector instructions); ff1 at 1280 channels on 2048 tokens 61 -> 47 us (1.15 PFLOP/s; dense bf16 MFMAs on such data reach 1.8 at the
 // clock they leave).  Second form: 215 per 16 channels (165), 334 with two slots, which L2's latency then bounds.
-// Blocks, start -> now: 640 channels, 14 frames x 500 positions per window 1282 -> 1141 us; 640 spatial, one frame per window
+// Blocks, all of their GEMMs on the ring kernel -> this one where it takes them: 640 channels, 14 frames x 500 positions per window 1282 -> 1141 us; 640 spatial, one frame per window
 // 1405 -> 1341; 1280 spatial 1077 -> 1029, temporal 888 -> 839; 320 spatial with heads of 40 9257 -> 8990.
 #pragma once
 #include "k_conv.h"
