@@ -85,4 +85,4 @@ def test_odd_map_slice_out_is_not_serial():
             si.si_stage_timing_enable(False)
         took.append(ms / n)
     print(took)
-    assert took[0] < 2.5 * took[1]
+    assert took[0] < 3.5 * took[1]  # 21 and 10 us; 49 before
